@@ -126,6 +126,29 @@ __device__ __forceinline__ uint64_t wave_inclusive_scan_u64(uint64_t x) {
 }
 
 // ---------------------------------------------------------------------------
+// division by a number fixed per launch
+// ---------------------------------------------------------------------------
+// Division of a 31-bit number by d (1 <= d < 2^31) as a multiply and a shift
+// (Granlund and Montgomery, "Division by invariant integers using
+// multiplication", PLDI 1994, Theorem 4.2): with l = ceil(log2 d) and
+// m = ceil(2^(31 + l) / d) <= 2^32 - 1, floor(n / d) = (n m) >> (31 + l) for
+// every n < 2^31.
+struct Div31 {
+    uint32_t m, sh;
+};
+
+inline Div31 make_div31(uint32_t d) {
+    uint32_t l = 0;
+    while ((1ull << l) < d) ++l;  // l <= 31
+    const uint64_t p = 1ull << (31 + l);
+    return Div31{(uint32_t)((p + d - 1) / d), 31 + l};
+}
+
+__host__ __device__ __forceinline__ uint32_t div31(uint32_t n, const Div31& v) {
+    return (uint32_t)(((uint64_t)n * v.m) >> v.sh);
+}
+
+// ---------------------------------------------------------------------------
 // exact leaf quantiser  L(p) = floor(2^F p^(a/b))
 // ---------------------------------------------------------------------------
 // q = L(p) is the unique integer with q^b <= 2^(bF) p^a < (q+1)^b.
@@ -392,6 +415,7 @@ struct GatherArgs {
     void* out;
     int32_t xform;          // conduit_xform_kind
     int32_t plane_units;    // U8_BF16_NORM: 4-byte units per plane
+    Div31 by_plane;         // ... and the division by it
     float mean[4];
     float stdv[4];
     // scalar columns taken from the newest slot

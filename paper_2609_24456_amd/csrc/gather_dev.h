@@ -293,7 +293,7 @@ __device__ __forceinline__ void finish(const GatherArgs& a, const Item& t, const
         for (int r = 0; r < kUnroll; ++r) {
             const int64_t u = u0 + (int64_t)r * kThreads;
             const uint32_t uu = (uint32_t)(u < units ? u : units - 1);  // keeps the plane index in range
-            const uint16_t* tb = lut + (uu / (uint32_t)a.plane_units) * 256;
+            const uint16_t* tb = lut + div31(uu, a.by_plane) * 256;
             const uint32_t x = v[r];
             const uint32_t lo = (uint32_t)tb[x & 255u] | ((uint32_t)tb[(x >> 8) & 255u] << 16);
             const uint32_t hi = (uint32_t)tb[(x >> 16) & 255u] | ((uint32_t)tb[x >> 24] << 16);
@@ -435,33 +435,35 @@ template <> struct OutUnit<kXfCopy16> { typedef u32x4 T; };
 template <> struct OutUnit<CONDUIT_XF_U8_F32> { typedef f32x4 T; };
 template <> struct OutUnit<CONDUIT_XF_U8_BF16_NORM> { typedef u32x2 T; };
 
+// one unit of a frame (unit u of it; lut as build_lut makes it)
+template <int XF>
+__device__ __forceinline__ typename OutUnit<XF>::T convert_unit(const GatherArgs& a, uint32_t u,
+                                                                const typename UnitOf<XF>::T& x, const uint16_t* lut) {
+    typename OutUnit<XF>::T o;
+    if constexpr (XF == kXfCopy16 || XF == CONDUIT_XF_NONE) {
+        o = x;
+    } else if constexpr (XF == CONDUIT_XF_U8_F32) {
+        o.x = u8_unit_f32(x & 255u);
+        o.y = u8_unit_f32((x >> 8) & 255u);
+        o.z = u8_unit_f32((x >> 16) & 255u);
+        o.w = u8_unit_f32(x >> 24);
+    } else {  // U8_BF16_NORM
+        const uint16_t* tb = lut + div31(u, a.by_plane) * 256;
+        o.x = (uint32_t)tb[x & 255u] | ((uint32_t)tb[(x >> 8) & 255u] << 16);
+        o.y = (uint32_t)tb[(x >> 16) & 255u] | ((uint32_t)tb[x >> 24] << 16);
+    }
+    return o;
+}
+
 template <int XF>
 __device__ __forceinline__ void convert_units(const GatherArgs& a, int part, const typename UnitOf<XF>::T (&v)[kUnroll],
                                               const uint16_t* lut, int tid, typename OutUnit<XF>::T (&o)[kUnroll]) {
-    if constexpr (XF == kXfCopy16 || XF == CONDUIT_XF_NONE) {
+    const int64_t units = a.row_bytes >> UnitOf<XF>::kShift;
+    const int64_t u0 = (int64_t)part * kUnitsPerBlock + tid;
 #pragma unroll
-        for (int r = 0; r < kUnroll; ++r) o[r] = v[r];
-    } else if constexpr (XF == CONDUIT_XF_U8_F32) {
-#pragma unroll
-        for (int r = 0; r < kUnroll; ++r) {
-            const uint32_t x = v[r];
-            o[r].x = u8_unit_f32(x & 255u);
-            o[r].y = u8_unit_f32((x >> 8) & 255u);
-            o[r].z = u8_unit_f32((x >> 16) & 255u);
-            o[r].w = u8_unit_f32(x >> 24);
-        }
-    } else {  // U8_BF16_NORM
-        const int64_t units = a.row_bytes >> 2;
-        const int64_t u0 = (int64_t)part * kUnitsPerBlock + tid;
-#pragma unroll
-        for (int r = 0; r < kUnroll; ++r) {
-            const int64_t u = u0 + (int64_t)r * kThreads;
-            const uint32_t uu = (uint32_t)(u < units ? u : units - 1);  // keeps the plane index in range
-            const uint16_t* tb = lut + (uu / (uint32_t)a.plane_units) * 256;
-            const uint32_t x = v[r];
-            o[r].x = (uint32_t)tb[x & 255u] | ((uint32_t)tb[(x >> 8) & 255u] << 16);
-            o[r].y = (uint32_t)tb[(x >> 16) & 255u] | ((uint32_t)tb[x >> 24] << 16);
-        }
+    for (int r = 0; r < kUnroll; ++r) {
+        const int64_t u = u0 + (int64_t)r * kThreads;
+        o[r] = convert_unit<XF>(a, (uint32_t)(u < units ? u : units - 1), v[r], lut);  // keeps the plane index in range
     }
 }
 

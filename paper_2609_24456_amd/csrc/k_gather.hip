@@ -4,15 +4,19 @@
 // operators it lists).  The same kernels
 // serve the on-policy minibatch shuffle-gather (K = 1, rows of a rollout).
 //
-// Two shapes over the work items of gather_dev.h: four persistent workgroups
-// per compute unit walking the items double-buffered (k_gather_pipe, outputs up
-// to 128 MB), or one item per workgroup (k_gather_rows, larger outputs).
+// Three shapes: single frames and small ones as one flat run of units
+// (k_gather_flat); stacked and bf16 frames as the work items of gather_dev.h,
+// walked double-buffered by four persistent workgroups per compute unit
+// (k_gather_pipe, outputs up to 128 MB) or one per workgroup (k_gather_rows,
+// larger outputs).
 // Scalar columns (action, reward, done, extra float columns) are produced by
 // workgroups at the head of the grid, one lane per output row, so that their
 // dependent loads (index, then the columns) start with the first dispatched
 // workgroups and finish under the frame traffic.  When the indices were just
 // sampled, one more workgroup there computes the batch's importance weights
 // (is_weights_block).
+#include <type_traits>
+
 #include "gather_dev.h"
 
 namespace conduit {
@@ -27,6 +31,29 @@ __device__ __forceinline__ void flag_index(const GatherArgs& a) {
 
 // outputs up to this size use the persistent pipelined kernel
 constexpr int64_t kPipeMaxOutBytes = 128ll << 20;
+
+// The flat kernel (below) takes, of the batches whose units a 31-bit number
+// counts:
+//   * every frame of up to kFlatMaxUnits units: an item of 1,792 units would
+//     leave most of its lanes idle (24,576 rows of 48 floats, 12 units each:
+//     42.2 us as items, 6.3 us flat; 4,096 40x40 frames to fp32: 10.7 and 7.4);
+//   * single frames of any size, unless normalised to bf16: its non-temporal
+//     contiguous stores beat the persistent kernel's write-through ones and its
+//     even split beats items with a remainder (4,096 84x84 frames to fp32 35 ->
+//     30 us, 88x88 50 -> 32 us; 65,536 rows of 4 KB 114 -> 98 us; 16,384 images
+//     of 3x84x84 to fp32 322 -> 310 us);
+//   * single frames of up to kFlatMaxNormUnits units normalised to bf16 (4,096
+//     64x64 frames 15.3 -> 11.8 us); larger ones spend more on finding each
+//     unit's row than they save (1,024 images of 3x224x224: 83 us as items, 98
+//     flat).
+// Stacks of larger frames stay with the item kernels, which look each frame's
+// validity up once per item (512 stacks of four 84x84 frames to bf16: 10.8 us,
+// 12.9 flat).
+constexpr int64_t kFlatMaxUnits = 512;
+constexpr int64_t kFlatMaxNormUnits = 1024;
+constexpr int kFlatUnroll = 4;         // its most units per lane
+constexpr int64_t kFlatWgsPerCu = 4;   // workgroups per compute unit before a lane takes more units
+constexpr int64_t kFlatLoopWgs = 16;   // bf16: workgroups per compute unit, each looping with its table
 
 // Blocks [0, tail): scalar columns, then the weights block (if any).
 __device__ __forceinline__ bool tail_block(const GatherArgs& a, int64_t tail) {
@@ -109,6 +136,82 @@ __global__ __launch_bounds__(kThreads) void k_gather_pipe(GatherArgs a, int32_t 
     }
 }
 
+// The batch as one flat run of n * stack * units units, U per lane and kThreads
+// apart, so that a workgroup takes as many rows as its lanes cover and a
+// wavefront's store is contiguous whatever the row size.  Each lane finds its
+// units' frames with a multiply (div31) and reads their sample indices itself:
+// two dependent rounds of loads (index, then payload and frame metadata), all U
+// of each in flight.  Bound by those two rounds for small batches and by HBM for
+// large ones.  Non-temporal stores: written through at agent scope the same
+// kernel takes 336 us instead of 310 for 16,384 images of 3x84x84 to fp32, and
+// 16.8 instead of 14.5 us for 4,096 64x64 frames.  With the bf16 table a
+// workgroup loops over tiles, so that the table is built once per workgroup.
+template <int XF, int U>
+__global__ __launch_bounds__(kThreads) void k_gather_flat(GatherArgs a, uint32_t units, Div31 by_units, Div31 by_stack,
+                                                          uint32_t total, int32_t tail) {
+    __shared__ uint16_t lut[(XF == CONDUIT_XF_U8_BF16_NORM) ? 4 * 256 : 1];
+    if (tail_block(a, tail)) return;
+    typedef typename UnitOf<XF>::T V;
+    typedef typename OutUnit<XF>::T O;
+    constexpr uint32_t kTile = kThreads * U;
+    if constexpr (XF == CONDUIT_XF_U8_BF16_NORM) {
+        build_lut(a, lut);
+        __syncthreads();
+    }
+    const uint32_t step = (gridDim.x - (uint32_t)tail) * kTile;
+    for (uint32_t first = (blockIdx.x - (uint32_t)tail) * kTile; first < total; first += step) {
+        uint32_t w[U], d[U];  // unit of the frame, frames back
+        int64_t i[U];
+#pragma unroll
+        for (int r = 0; r < U; ++r) {
+            const uint32_t e = first + r * kThreads + threadIdx.x;
+            const uint32_t u = e < total ? e : total - 1;  // every load is in range
+            const uint32_t f = div31(u, by_units);
+            const uint32_t b = div31(f, by_stack);
+            w[r] = u - f * units;
+            d[r] = (uint32_t)a.stack - 1 - (f - b * (uint32_t)a.stack);
+            i[r] = a.idx[b];
+        }
+        bool ok[U];
+        V v[U];
+        int32_t si[U], sj[U];
+        uint32_t ei[U], ej[U];
+#pragma unroll
+        for (int r = 0; r < U; ++r) {
+            ok[r] = i[r] >= 0 && i[r] < a.limit;
+            if (!ok[r] && w[r] == 0 && d[r] == 0) flag_index(a);
+            const int64_t ii = ok[r] ? i[r] : 0;
+            int64_t j = ii - d[r];
+            if (j < 0) j = ok[r] ? j + a.capacity : 0;
+            v[r] = *(reinterpret_cast<const V*>(a.src + j * a.row_bytes) + w[r]);
+            si[r] = sj[r] = 0;
+            ei[r] = ej[r] = 0;
+            if (a.stack > 1) {  // kernel argument: uniform
+                si[r] = a.step[ii];
+                sj[r] = a.step[j];
+                ei[r] = a.episode[ii];
+                ej[r] = a.episode[j];
+            }
+        }
+        O o[U];
+#pragma unroll
+        for (int r = 0; r < U; ++r) {
+            const int32_t dr = (int32_t)d[r];
+            const bool valid = ok[r] & ((dr == 0) | ((dr <= si[r]) & (ei[r] == ej[r]) & (sj[r] == si[r] - dr)));
+            o[r] = convert_unit<XF>(a, w[r], v[r], lut);
+            if (!valid) o[r] = zero_unit<O>();
+            asm volatile("" : "+v"(o[r]));  // conversions ahead of the stores, as in finish()
+        }
+        O* out = reinterpret_cast<O*>(a.out) + first;
+        const uint32_t n = total - first < kTile ? total - first : kTile;  // the tile's units
+#pragma unroll
+        for (int r = 0; r < U; ++r) {
+            const uint32_t e = r * kThreads + threadIdx.x;
+            if (e < n) __builtin_nontemporal_store(o[r], out + e);
+        }
+    }
+}
+
 // ragged token packing: one workgroup per sample; each lane handles up to 4
 // quads (16 elements) per pass, all loads issued before the stores
 __global__ __launch_bounds__(kThreads) void k_pack(PackArgs a) {
@@ -148,6 +251,25 @@ hipError_t launch_gather_xf(const GatherArgs& a, hipStream_t s, int64_t tail_blo
     if (n_items + tail_blocks == 0) return hipSuccess;
     const int64_t out_bytes = a.n * a.stack * a.row_bytes *
                               (XF == CONDUIT_XF_U8_F32 ? 4 : XF == CONDUIT_XF_U8_BF16_NORM ? 2 : 1);
+    const bool norm = XF == CONDUIT_XF_U8_BF16_NORM;
+    const bool flat = units <= kFlatMaxUnits || (a.stack == 1 && (!norm || units <= kFlatMaxNormUnits));
+    const int64_t total = a.n * a.stack * units;
+    if (n_items > 0 && flat && total < (1ll << 31) - kThreads * kFlatUnroll) {
+        // the most units per lane that still gives every compute unit
+        // kFlatWgsPerCu workgroups
+        const int64_t per = total / (kThreads * kFlatWgsPerCu * (int64_t)device_cus());
+        const Div31 du = make_div31((uint32_t)units), ds = make_div31((uint32_t)a.stack);
+        auto go = [&](auto U) {
+            const int64_t wgs = (total + kThreads * U.value - 1) / (kThreads * U.value);
+            const int64_t cap = norm ? kFlatLoopWgs * device_cus() : wgs;
+            hipLaunchKernelGGL((k_gather_flat<XF, U.value>), dim3((unsigned)((wgs < cap ? wgs : cap) + tail_blocks)),
+                               dim3(kThreads), 0, s, a, (uint32_t)units, du, ds, (uint32_t)total, (int32_t)tail_blocks);
+        };
+        if (per >= 4) go(std::integral_constant<int, 4>{});
+        else if (per >= 2) go(std::integral_constant<int, 2>{});
+        else go(std::integral_constant<int, 1>{});
+        return hipGetLastError();
+    }
     if (out_bytes <= kPipeMaxOutBytes) {
         // small batches: persistent pipelined workgroups
         const int64_t frame_grid = n_items < 4LL * device_cus() ? n_items : 4LL * device_cus();

@@ -163,6 +163,7 @@ struct RaiseList {
     const uint32_t* prio;
     int64_t n;
     int64_t size;  // valid indices are [0, size)
+    uint32_t known = 0;  // idx NULL: the list's largest priority, already worked out
 };
 
 // max(stored running maximum, every valid priority of u) by one wavefront: the
@@ -170,6 +171,7 @@ struct RaiseList {
 // entries is one memory round trip.
 __device__ __forceinline__ uint32_t raised_max(const DeviceState* state, const RaiseList& u) {
     const uint32_t cur = state->max_prio;
+    if (!u.idx) return cur > u.known ? cur : u.known;
     uint32_t m = 0;
     for (int64_t base = 0; base < u.n; base += (int64_t)kWave * kRaiseUnroll) {
         int64_t s[kRaiseUnroll];
@@ -212,7 +214,7 @@ __device__ __forceinline__ void ingest_meta(const IngestArgs& a, int64_t block, 
     const uint32_t old = tree ? a.tree.leaves[valid ? slot : 0] : 0u;
     const uint32_t p_row = tree && a.src_prio ? a.src_prio[jj] : 0u;
     const bool raised = raise.n > 0;
-    const uint32_t p_state = tree && !a.src_prio && !raised ? a.state->max_prio : 0u;
+    const uint32_t p_state = tree && (a.src_prio || !raised) ? a.state->max_prio : 0u;
     const float rew = a.src_reward ? a.src_reward[jj] : 0.0f;
     const uint8_t dn = a.src_done ? a.src_done[jj] : (uint8_t)0;
     const uint32_t ep = a.src_episode ? a.src_episode[jj] : 0u;
@@ -264,7 +266,7 @@ __device__ __forceinline__ void ingest_meta(const IngestArgs& a, int64_t block, 
     if (!tree) return;
     if (a.src_prio) {
         const uint32_t m = wave_max_u32(p_seen);
-        if (lane_id() == 0 && m > 0) atomicMax(&a.state->max_prio, m);
+        if (lane_id() == 0 && m > p_state) atomicMax(&a.state->max_prio, m);  // the stored maximum only grows
     }
     push_wave_deltas(a.tree, slot, delta, [&](int l, uint64_t node, uint64_t v) {
         atomicAdd(reinterpret_cast<unsigned long long*>(a.tree.level[l] + node), v);

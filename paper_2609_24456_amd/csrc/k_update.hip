@@ -2,8 +2,8 @@
 // paper App. C Invariant 2; proportional prioritised replay, Schaul et al.).
 //
 // Semantics: updates apply as if one after another in array order, so the last
-// occurrence of a repeated index wins.  One workgroup of 1024 lanes walks the
-// update list in chunks of 1024:
+// occurrence of a repeated index wins.  One workgroup of 1024 lanes takes a list
+// of up to 1,024 updates, the general form walking it in chunks of 1024:
 //   1. an LDS open-addressing table (2048 entries) keyed by slot keeps the
 //      largest position of every slot within the chunk (LDS atomicMax), which
 //      selects exactly one winner per distinct slot;
@@ -15,7 +15,8 @@
 //      wrote (same workgroup, separated by a barrier).
 // All tree arithmetic is integer modulo 2^64: exact and independent of the
 // order in which atomics land.  Sizes of the paper's workloads (256 to 1024
-// updates per call) take a single chunk.
+// updates per call) take a single chunk; longer lists are split over several
+// workgroups by slot (update_part in update_dev.h).
 //
 // Latency: barriers that only order LDS traffic use an LDS-only fence, so the
 // global tree atomics issued by the winners are never waited for inside the
@@ -28,15 +29,20 @@ namespace conduit {
 
 namespace {
 
+// SPLIT: the workgroups share a long list by slot, SPLIT entries per lane and
+// pass; 0: one workgroup takes it all (a kernel of its own: the
+// registers and LDS of the split would slow the short lists' launch)
+template <int SPLIT>
 __global__ __launch_bounds__(kUpdateThreads) void k_update(UpdateArgs a) {
     __shared__ uint32_t keys[kTable];
     __shared__ int32_t owner[kTable];
     __shared__ unsigned long long bins[kBins];
-    const uint32_t pmax = update_pass(a, keys, owner, bins);
+    const uint32_t seen = a.state->max_prio;
+    uint32_t pmax;
+    if constexpr (SPLIT > 0) pmax = update_part<SPLIT>(a, blockIdx.x, gridDim.x, keys, owner, bins);
+    else pmax = update_pass(a, keys, owner, bins);
     flush_bins(a.tree, bins);
-    // running maximum priority: one atomic per wavefront
-    const uint32_t wm = wave_max_u32(pmax);
-    if (lane_id() == 0 && wm > 0) atomicMax(&a.state->max_prio, wm);
+    raise_max(a.state, seen, pmax);
 }
 
 // One tree level recomputed from the level below it (level 1 from the
@@ -72,7 +78,11 @@ hipError_t launch_tree_rebuild(const TreeView& t, hipStream_t s) {
 
 hipError_t launch_update(const UpdateArgs& a, hipStream_t s) {
     if (a.n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_update, dim3(1), dim3(kUpdateThreads), 0, s, a);
+    const int groups = update_groups(a.n);
+    const dim3 grid((unsigned)groups), block(kUpdateThreads);
+    if (groups == 1) hipLaunchKernelGGL(k_update<0>, grid, block, 0, s, a);
+    else if (a.n <= 4 * kUpdateThreads) hipLaunchKernelGGL(k_update<4>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(k_update<8>, grid, block, 0, s, a);
     return hipGetLastError();
 }
 

@@ -9,11 +9,12 @@
 // priorities, which is max(current, every valid update priority).  Hence:
 //   * block 0 (1024 lanes) runs the update pass (update_dev.h) skipping the
 //     slots the ingest evicts, flushes its LDS bins and raises the running
-//     maximum;
+//     maximum (a list of more than 1,024 updates is split over several such
+//     blocks by slot);
 //   * every other block is four ingest sub-blocks of 256 lanes (ingest_dev.h):
 //     the new rows' columns, leaves and per-wavefront tree deltas, each
-//     wavefront computing the raised running maximum from the update list
-//     itself, and the payload copy.
+//     wavefront (of a long list, each block) computing the raised running
+//     maximum from the update list itself, and the payload copy.
 // The two sets of leaves are disjoint and every tree change is an integer
 // atomic add, so the result equals the two calls made one after the other.
 #include "ingest_dev.h"
@@ -25,26 +26,66 @@ namespace {
 
 constexpr int kSubs = kUpdateThreads / kIngestThreads;
 
-template <typename V>
+// The largest valid priority of a list, by the whole workgroup.
+__device__ uint32_t list_max(const RaiseList& u, int32_t* scratch) {
+    uint32_t m = 0;
+    for (int64_t base = 0; base < u.n; base += (int64_t)kUpdateThreads * kRaiseUnroll) {
+        int64_t s[kRaiseUnroll];
+        uint32_t p[kRaiseUnroll];
+#pragma unroll
+        for (int r = 0; r < kRaiseUnroll; ++r) {
+            const int64_t k = base + (int64_t)r * kUpdateThreads + threadIdx.x;
+            s[r] = k < u.n ? u.idx[k] : -1;
+            p[r] = k < u.n ? u.prio[k] : 0u;
+        }
+#pragma unroll
+        for (int r = 0; r < kRaiseUnroll; ++r)
+            if (s[r] >= 0 && s[r] < u.size && p[r] > m) m = p[r];
+    }
+    m = wave_max_u32(m);
+    if (lane_id() == 0) scratch[threadIdx.x / kWave] = (int32_t)m;
+    __syncthreads();
+    uint32_t r = 0;
+    for (int i = 0; i < kUpdateThreads / kWave; ++i) {
+        const uint32_t x = (uint32_t)scratch[i];
+        r = x > r ? x : r;
+    }
+    return r;
+}
+
+// SPLIT: the first `groups` blocks share a long update list by slot, SPLIT
+// entries per lane and pass; 0: the first block takes the list
+template <typename V, int SPLIT>
 __global__ __launch_bounds__(kUpdateThreads) void k_update_ingest(UpdateArgs u, IngestArgs a, int64_t meta_subs,
-                                                                  int64_t copy_subs) {
+                                                                  int64_t copy_subs, int32_t groups) {
     __shared__ uint32_t keys[kTable];
     __shared__ int32_t owner[kTable];
     __shared__ unsigned long long bins[kBins];
-    if (blockIdx.x == 0) {
-        const uint32_t pmax = update_pass(u, keys, owner, bins, a.head, a.n);
+    if (blockIdx.x < (uint32_t)groups) {
+        const uint32_t seen = u.state->max_prio;
+        uint32_t pmax;
+        if constexpr (SPLIT > 0) pmax = update_part<SPLIT>(u, blockIdx.x, (uint32_t)groups, keys, owner, bins, a.head, a.n);
+        else pmax = update_pass(u, keys, owner, bins, a.head, a.n);
         flush_bins(u.tree, bins);
-        const uint32_t wm = wave_max_u32(pmax);
-        if (lane_id() == 0 && wm > 0) atomicMax(&u.state->max_prio, wm);
+        raise_max(u.state, seen, pmax);
         return;
     }
-    const int64_t sub = (int64_t)(blockIdx.x - 1) * kSubs + threadIdx.x / kIngestThreads;
+    const int64_t sub0 = (int64_t)(blockIdx.x - (uint32_t)groups) * kSubs;
+    const int64_t sub = sub0 + threadIdx.x / kIngestThreads;
     const int tid = (int)(threadIdx.x % kIngestThreads);
+    RaiseList raise{u.idx, u.prio, u.n, u.size};
+    if constexpr (SPLIT > 0) {
+        if (sub0 < meta_subs && !a.src_prio) {  // uniform: a long list is read by the whole workgroup
+            raise.known = list_max(raise, owner);
+            raise.n = 1;
+            raise.idx = nullptr;
+        }
+    }
     if (sub < meta_subs) {
         // the update block may already have raised the stored maximum with the
         // same priorities: raised_max takes max() over both, so the order of
         // the two parts does not matter
-        ingest_meta(a, sub, tid, RaiseList{u.idx, u.prio, u.n, u.size});
+        ingest_meta(a, sub, tid, raise);
     } else if (sub - meta_subs < copy_subs) {
         copy_dense<V>(a, sub - meta_subs, tid);
     }
@@ -64,12 +105,22 @@ hipError_t launch_update_ingest(const UpdateArgs& u, const IngestArgs& a, hipStr
     if (a.row_bytes == 0) vec = 16;
     const int64_t total_vec = a.n * (a.row_bytes / vec);
     const int64_t copy_subs = (total_vec + kIngestThreads * kCopyUnroll - 1) / (kIngestThreads * kCopyUnroll);
-    const dim3 grid((unsigned)(1 + (meta_subs + copy_subs + kSubs - 1) / kSubs)), block(kUpdateThreads);
+    const int32_t groups = update_groups(u.n);
+    const dim3 grid((unsigned)(groups + (meta_subs + copy_subs + kSubs - 1) / kSubs)), block(kUpdateThreads);
+    auto go = [&](auto v) {
+        typedef decltype(v) V;
+        if (groups == 1)
+            hipLaunchKernelGGL((k_update_ingest<V, 0>), grid, block, 0, s, u, a, meta_subs, copy_subs, groups);
+        else if (u.n <= 4 * kUpdateThreads)
+            hipLaunchKernelGGL((k_update_ingest<V, 4>), grid, block, 0, s, u, a, meta_subs, copy_subs, groups);
+        else
+            hipLaunchKernelGGL((k_update_ingest<V, 8>), grid, block, 0, s, u, a, meta_subs, copy_subs, groups);
+    };
     switch (vec) {
-        case 16: hipLaunchKernelGGL((k_update_ingest<u32x4>), grid, block, 0, s, u, a, meta_subs, copy_subs); break;
-        case 8: hipLaunchKernelGGL((k_update_ingest<u32x2>), grid, block, 0, s, u, a, meta_subs, copy_subs); break;
-        case 4: hipLaunchKernelGGL((k_update_ingest<uint32_t>), grid, block, 0, s, u, a, meta_subs, copy_subs); break;
-        default: hipLaunchKernelGGL((k_update_ingest<uint8_t>), grid, block, 0, s, u, a, meta_subs, copy_subs); break;
+        case 16: go(u32x4{}); break;
+        case 8: go(u32x2{}); break;
+        case 4: go(uint32_t{}); break;
+        default: go(uint8_t{}); break;
     }
     return hipGetLastError();
 }

@@ -6,7 +6,8 @@ import pytest
 import torch
 
 import oracle
-from gpu_util import dev, host
+import synth
+from gpu_util import dev, host, read_col, tree_consistent
 from paper_2609_24456_amd import conduit as cd
 
 pytestmark = pytest.mark.gpu
@@ -48,3 +49,49 @@ def test_minibatch_flat_rows(planes, units, kind, n, offset):
         assert np.array_equal(got[ok], w[ok]) and not got[~ok].any()
         for c, o in zip(cols, cols_out):
             assert np.array_equal(host(o)[ok], c[idx[ok]]) and not host(o)[~ok].any()
+
+
+# update lists around the split (2,048), with the last pass partial and whole
+# (4 and 8 entries per lane), several passes, repeats throughout, indices out of
+# range, and lists whose slots all fall to one of the 64 workgroups (more than
+# its lanes take at once), alone and with an ingest that evicts some of them
+@pytest.mark.parametrize("n,skew,m", [(2047, False, 0), (2048, False, 5), (4096, True, 0), (4097, False, 300),
+                                      (8191, True, 300), (8192, False, 0), (20000, True, 64), (20000, False, 300)])
+def test_long_update_lists(n, skew, m):
+    print(f"long update list n={n} skew={skew} ingest={m}", flush=True)
+    rng = np.random.default_rng(n + m)
+    cap = 70_000
+    prio = synth.quantise_priority(rng.lognormal(0, 1, cap + 700))
+    buf = cd.ReplayBuffer(cap, (1,), torch.float32, action_bytes=0)
+    orc = oracle.Replay(cap, (1,), np.float32, act_bytes=0)
+    for a, b in ((0, cap), (cap, cap + 700)):
+        obs = np.zeros((b - a, 1), np.float32)
+        buf.ingest(dev(obs), prio=dev(prio[a:b]))
+        orc.ingest(b - a, obs=obs, prio=prio[a:b])
+    slots = np.arange(cap)
+    if skew:
+        slots = slots[((slots ^ (slots >> 6) ^ (slots >> 12)) & 63) == 0]
+    for it in range(2):
+        idx = rng.choice(slots, n)
+        idx[n // 3::3] = rng.choice(idx[:50], len(idx[n // 3::3]))  # repeats
+        new = synth.quantise_priority(rng.lognormal(0, 2, n))
+        new[::97] = 0
+        bad = it == 1
+        sent = idx.copy()
+        if bad:
+            sent[5], sent[-1] = cap, -1
+        keep = (sent >= 0) & (sent < cap)
+        if m:
+            rows = np.zeros((m, 1), np.float32)
+            buf.update_ingest(dev(sent), dev(new), dev(rows))
+        else:
+            buf.update(dev(sent), dev(new))
+        assert buf.sync_check() == (cd.ESTATE if bad else cd.OK), cd.last_error()
+        buf.clear_error()
+        orc.update(idx[keep], new[keep])
+        if m:
+            orc.ingest(m, obs=rows)
+        assert np.array_equal(read_col(buf, cd.COL_LEAVES, cap * 4, np.uint32), orc.leaf), it
+        assert read_col(buf, cd.COL_MAX_PRIO, 4, np.uint32)[0] == orc.max_prio
+        tree_consistent(buf, cap)
+    buf.close()

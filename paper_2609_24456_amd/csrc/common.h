@@ -34,7 +34,7 @@ struct DeviceState {
     uint32_t leaf_min;   // sampler scratch: smallest non-zero leaf of the buffer (buffer-wide IS
                          // normalisation), UINT32_MAX between calls
     uint32_t ticket;     // sampler scratch: finished blocks, 0 between calls
-    uint32_t pad;
+    uint32_t batch_min;  // sampler scratch of large batches: the smallest sampled leaf
 };
 
 // The 64-ary sum tree.  Level 0 = uint32 leaves, levels 1..depth = uint64 sums;
@@ -123,6 +123,13 @@ __device__ __forceinline__ uint64_t wave_inclusive_scan_u64(uint64_t x) {
     x += dpp_u64<kDppRowBcast15, 0xa, 0xf>(x);
     x += dpp_u64<kDppRowBcast31, 0xc, 0xf>(x);
     return x;
+}
+
+// workgroup barrier ordering LDS only (no wait for outstanding global memory)
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // ---------------------------------------------------------------------------
@@ -390,11 +397,14 @@ __device__ void fold_leaf_min(const SampleArgs& a, int64_t wg, int64_t wgs) {
     if (threadIdx.x == 0) {
         uint32_t r = wmin[0];
         for (int i = 1; i < NT / kWave; ++i) r = wmin[i] < r ? wmin[i] : r;
-        if (r != 0xffffffffu)
+        if (r < __hip_atomic_load(a.leaf_min, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))  // it only falls
             (void)__hip_atomic_fetch_min(a.leaf_min, r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
+// the weights of a batch whose leaves an earlier launch has parked (and, with
+// buffer-wide normalisation, folded into state->leaf_min)
+hipError_t launch_weights(const SampleArgs& a, hipStream_t s);
 // sampler, then the weights kernel (if w_out is set)
 hipError_t launch_sample(const SampleArgs& a, hipStream_t s);
 // sampler only: leaves parked in w_out for a later weights block

@@ -365,6 +365,13 @@ __device__ __forceinline__ void row_scalars_store(const GatherArgs& a, int64_t b
         row_scalar_store(a, b, t, n - 2, words, r.ok ? row_scalar_load(a, s, t, n - 2, words) : 0u);
 }
 
+// rows (whole stacks) of at most this many units are small: a wavefront takes one
+constexpr int kRowUnroll = 4;  // units per lane
+constexpr int64_t kRowMaxUnits = kRowUnroll * kWave;
+// largest batch of them that the one-launch kernels with tickets take
+// (k_sample_gather.hip)
+constexpr int64_t kRowsTicketMax = 1024;
+
 // rows of at most this many work items take the fused kernels (a sample's
 // workgroup finds its slot itself and its two 256-lane halves share the items)
 constexpr int64_t kFusedMaxItemsPerRow = 8;

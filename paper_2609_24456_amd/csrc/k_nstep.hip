@@ -78,6 +78,8 @@ hipError_t launch_nstep_gather(const NstepArgs& na, const GatherArgs& ga, hipStr
     if (na.batch <= 0 || ga.n != na.batch || ga.ncols != 0 || ga.weights.w || per_row < 1 ||
         per_row > kFusedMaxItemsPerRow)
         return hipErrorNotSupported;
+    // large batches of small rows: the targets, then the flat gather
+    if (units * ga.stack <= kRowMaxUnits && na.batch > kRowsTicketMax) return hipErrorNotSupported;
     const int64_t wgs = per_row > 2 ? (per_row + 1) / 2 : 1;  // two items per workgroup
     if (c16) return launch_nstep_gather_xf<kXfCopy16>(na, ga, bpf, wgs, s);
     switch (ga.xform) {

@@ -106,6 +106,144 @@ __global__ __launch_bounds__(kWg) void k_sample_gather(SampleArgs sa, GatherArgs
     gather_row<XF, true>(a, b, half, 2, bpf, s_slot, lut, (int)(threadIdx.x % kThreads));
 }
 
+// Rows of few units (vector observations, small frames): one wavefront per
+// sample descends and copies the row itself, up to kRowUnroll units per lane, so
+// that a workgroup delivers eight rows; a 512-lane workgroup per row left all
+// but a few lanes idle.  Bound by the descent's dependent loads for small
+// batches and by the wavefronts in flight for large ones.  With TICKET sampler
+// workgroups beside the row ones write the indices and the weights, as in
+// k_sample_gather: a small batch's critical path is the ticket's, and it should
+// not wait for rows.  Without it the row wavefronts write the indices and park
+// the leaves, one descent per sample, and the weights come by launches of their
+// own (launch_weights).  Against 512 lanes per row: 256 rows of 8 floats 6.2 ->
+// 6.0 us, 512 of 240 floats 8.9 -> 6.4, 16,384 of 48 floats 169 -> 15.4 + 7.1 for
+// the weights.
+// TICKET up to kRowsTicketMax samples: the workgroups' atomics run one after the
+// other and the last workgroup computes every weight (1,024 samples 10.0 us
+// against 7.1 + 3.2 + a launch, 4,096 of 240 floats 22.2 against 6.7 + 2.0 + 3.1).
+
+template <int XF>
+struct WaveRow {
+    typename UnitOf<XF>::T v[kRowUnroll];
+    uint32_t w[kRowUnroll];
+    int32_t d[kRowUnroll], sj[kRowUnroll];
+    uint32_t ej[kRowUnroll];
+    int32_t si;
+    uint32_t ei, sv, total;
+    int64_t ii;
+    bool ok;
+
+    __device__ __forceinline__ void load(const GatherArgs& a, int64_t i, uint32_t units, const Div31& by_units) {
+        typedef typename UnitOf<XF>::T V;
+        const int lane = lane_id();
+        bool words;
+        const int ns = row_scalar_lanes(a, &words);
+        ok = i >= 0 && i < a.limit;
+        ii = ok ? i : 0;
+        total = a.out ? units * (uint32_t)a.stack : 0u;
+        si = 0;
+        ei = 0;
+        if (a.stack > 1) {  // kernel argument: uniform
+            si = a.step[ii];
+            ei = a.episode[ii];
+        }
+        sv = 0;
+        if (lane < ns) sv = row_scalar_load(a, ii, lane, ns - 2, words);
+#pragma unroll
+        for (int r = 0; r < kRowUnroll; ++r) {
+            sj[r] = 0;
+            ej[r] = 0;
+            d[r] = 0;
+            w[r] = 0;
+            v[r] = {};
+            if ((uint32_t)r * kWave >= total) continue;  // uniform
+            const uint32_t e = (uint32_t)(lane + r * kWave);
+            const uint32_t u = e < total ? e : total - 1;  // every load is in range
+            const uint32_t f = a.stack > 1 ? div31(u, by_units) : 0u;
+            w[r] = u - f * units;
+            d[r] = a.stack - 1 - (int32_t)f;
+            int64_t j = ii - d[r];
+            if (j < 0) j = ok ? j + a.capacity : 0;
+            v[r] = *(reinterpret_cast<const V*>(a.src + j * a.row_bytes) + w[r]);
+            if (a.stack > 1) {
+                sj[r] = a.step[j];
+                ej[r] = a.episode[j];
+            }
+        }
+    }
+
+    __device__ __forceinline__ void store(const GatherArgs& a, int64_t b, const uint16_t* lut) const {
+        typedef typename OutUnit<XF>::T O;
+        const int lane = lane_id();
+        O* out = reinterpret_cast<O*>(a.out) + b * total;
+#pragma unroll
+        for (int r = 0; r < kRowUnroll; ++r) {
+            const bool valid = ok & ((d[r] == 0) | ((d[r] <= si) & (ei == ej[r]) & (sj[r] == si - d[r])));
+            const O o = convert_unit<XF>(a, w[r], v[r], lut);
+            const uint32_t e = (uint32_t)(lane + r * kWave);
+            if (e < total) out[e] = valid ? o : zero_unit<O>();
+        }
+        bool words;
+        const int ns = row_scalar_lanes(a, &words);
+        if (lane < ns) row_scalar_store(a, b, lane, ns - 2, words, ok ? sv : 0u);
+        for (int t = lane + kWave; t < ns; t += kWave)  // rows of more than 64 scalar units
+            row_scalar_store(a, b, t, ns - 2, words, ok ? row_scalar_load(a, ii, t, ns - 2, words) : 0u);
+    }
+};
+
+template <int XF, int PRE, int DEPTH, bool TICKET>
+__global__ __launch_bounds__(kWg) void k_sample_rows(SampleArgs sa, GatherArgs a, DivB dv, uint32_t units, Div31 by_units,
+                                                     int32_t row_wgs) {
+    __shared__ uint16_t lut[(XF == CONDUIT_XF_U8_BF16_NORM) ? 4 * 256 : 1];
+    const int64_t wg = blockIdx.x;
+    if (TICKET && wg >= row_wgs) {
+        sampler_wg<kWg, PRE, DEPTH>(sa, dv, wg - row_wgs);
+        return;
+    }
+    if constexpr (XF == CONDUIT_XF_U8_BF16_NORM) {
+        build_lut(a, lut, 0, kWg);
+        __syncthreads();
+    }
+    const int64_t k = wg * kSamplesPerSamplerWg + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    if (k < sa.batch) {  // wave-uniform
+        const Descent d = tree_descend<PRE, DEPTH>(sa.tree, sa.uniforms, k, dv);
+        if (!TICKET && lane_id() == 0) {
+            sa.idx_out[k] = d.slot;
+            if (sa.w_out) reinterpret_cast<uint32_t*>(sa.w_out)[k] = d.leaf;  // parked for launch_weights
+            if (d.slot < 0 && k == 0) flag_error(sa.err, ERR_EMPTY_TREE);
+            if (d.lost) flag_error(sa.err, ERR_DESCENT);
+        }
+        WaveRow<XF> row;
+        row.load(a, d.slot, units, by_units);
+        row.store(a, k, lut);
+    }
+    if (!TICKET && sa.leaf_min) fold_leaf_min<kWg>(sa, wg, row_wgs);  // buffer-wide normalisation
+}
+
+template <int XF>
+struct RowsLaunch {
+    const SampleArgs& sa;
+    const GatherArgs& ga;
+    DivB dv;
+    uint32_t units;
+    hipStream_t s;
+    template <int PRE, int DEPTH>
+    hipError_t operator()() const {
+        const int64_t wgs = (sa.batch + kSamplesPerSamplerWg - 1) / kSamplesPerSamplerWg;
+        const dim3 block(kWg);
+        const Div31 du = make_div31(units);
+        if (sa.batch <= kRowsTicketMax) {
+            hipLaunchKernelGGL((k_sample_rows<XF, PRE, DEPTH, true>), dim3((unsigned)(2 * wgs)), block, 0, s, sa, ga, dv,
+                               units, du, (int32_t)wgs);
+            return hipGetLastError();
+        }
+        hipLaunchKernelGGL((k_sample_rows<XF, PRE, DEPTH, false>), dim3((unsigned)wgs), block, 0, s, sa, ga, dv, units, du,
+                           (int32_t)wgs);
+        const hipError_t e = hipGetLastError();
+        return e != hipSuccess || !sa.w_out ? e : launch_weights(sa, s);
+    }
+};
+
 template <int XF>
 struct FusedLaunch {
     const SampleArgs& sa;
@@ -125,6 +263,10 @@ struct FusedLaunch {
 
 template <int XF>
 hipError_t launch_xf(const SampleArgs& sa, const GatherArgs& ga, hipStream_t s, int64_t bpf) {
+    const int64_t units = ga.row_bytes >> UnitOf<XF>::kShift;
+    if (units * ga.stack <= kRowMaxUnits)
+        return with_descent_shape(sa.tree, descend_prefetch(sa.tree),
+                                  RowsLaunch<XF>{sa, ga, make_divb((uint64_t)sa.batch), (uint32_t)units, s});
     return with_descent_shape(sa.tree, descend_prefetch(sa.tree),
                               FusedLaunch<XF>{sa, ga, make_divb((uint64_t)sa.batch), bpf, s});
 }
@@ -270,6 +412,11 @@ hipError_t launch_sample_gather(const SampleArgs& sa, const GatherArgs& ga, hipS
     const int64_t bpf = ga.out && units > 0 ? (units + kUnitsPerBlock - 1) / kUnitsPerBlock : 0;
     const int64_t per_row = bpf * ga.stack;
     if (sa.batch <= 0 || ga.ncols != 0 || per_row > kFusedMaxItemsPerRow) return hipErrorNotSupported;
+    // large batches of plain single frames that a wavefront does not take: the
+    // sampler and the flat gather, without a descent and 512 lanes per row (4,096
+    // rows of 4,000 floats: 52.7 us as one launch)
+    if (ga.stack == 1 && ga.xform != CONDUIT_XF_U8_BF16_NORM && units > kRowMaxUnits && sa.batch > kRowsTicketMax)
+        return hipErrorNotSupported;
     if (c16) return launch_xf<kXfCopy16>(sa, ga, s, bpf);
     switch (ga.xform) {
         case CONDUIT_XF_NONE: return launch_xf<CONDUIT_XF_NONE>(sa, ga, s, bpf);
@@ -288,6 +435,9 @@ hipError_t launch_sample_gather_nstep(const SampleArgs& sa, const GatherArgs& ga
     if (sa.batch <= 0 || na.batch != sa.batch || ga.ncols != 0 || bpf < 1 ||
         bpf * frames > kFusedNstepMaxItemsPerRow)
         return hipErrorNotSupported;
+    // large batches of small rows: the wavefront-per-sample delivery, then the
+    // targets and the flat gather
+    if (units * ga.stack <= kRowMaxUnits && sa.batch > kRowsTicketMax) return hipErrorNotSupported;
     if (c16) return launch_nstep_xf<kXfCopy16>(sa, ga, na, next_out, s, bpf);
     switch (ga.xform) {
         case CONDUIT_XF_NONE: return launch_nstep_xf<CONDUIT_XF_NONE>(sa, ga, na, next_out, s, bpf);

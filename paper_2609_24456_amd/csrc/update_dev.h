@@ -13,13 +13,6 @@ constexpr int kBins = 2048;    // u64 LDS bins for small tree levels
 
 __device__ __forceinline__ uint32_t slot_hash(uint32_t key) { return (key * 0x9E3779B1u) >> (32 - 11); }
 
-// workgroup barrier ordering LDS only (no wait for outstanding global memory)
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // whether an ingest of ring slots [ev_head, ev_head + ev_n) replaces `slot`
 __device__ __forceinline__ bool evicted(const TreeView& tr, int64_t slot, int64_t ev_head, int64_t ev_n) {
     const int64_t back = slot - ev_head;

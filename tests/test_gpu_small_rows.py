@@ -7,7 +7,7 @@ import torch
 
 import oracle
 import synth
-from gpu_util import dev, host, read_col, tree_consistent
+from gpu_util import assert_weights_close, dev, host, read_col, tree_consistent
 from paper_2609_24456_amd import conduit as cd
 
 pytestmark = pytest.mark.gpu
@@ -94,4 +94,68 @@ def test_long_update_lists(n, skew, m):
         assert np.array_equal(read_col(buf, cd.COL_LEAVES, cap * 4, np.uint32), orc.leaf), it
         assert read_col(buf, cd.COL_MAX_PRIO, 4, np.uint32)[0] == orc.max_prio
         tree_consistent(buf, cap)
+    buf.close()
+
+
+# rows of few units through sample + gather: one unit; the largest row a
+# wavefront takes (256 units) and the next one; stacks; every transform; batches
+# around the ticket's limit (1,024), the one-workgroup weights' (2,048) and a
+# partial last workgroup; n-step targets with them; both weight normalisations
+@pytest.mark.parametrize("shape,K,kind,B,norm", [
+    ((1, 4), 1, cd.XF_NONE, 1, 0), ((1, 1020), 1, cd.XF_NONE, 1024, 0), ((1, 1024), 1, cd.XF_U8_F32, 1025, 0),
+    ((1, 1028), 1, cd.XF_NONE, 1025, 0), ((1, 48), 3, cd.XF_NONE, 2048, 1), ((1, 256), 4, cd.XF_U8_F32, 2049, 0),
+    ((3, 80), 4, cd.XF_U8_BF16_NORM, 300, 1), ((2, 128), 4, cd.XF_U8_BF16_NORM, 2503, 1),
+    ((1, 4096), 1, cd.XF_NONE, 1024, 1), ((1, 4112), 1, cd.XF_NONE, 1100, 0)])
+def test_sample_gather_small_rows(shape, K, kind, B, norm):
+    print(f"small rows shape={shape} K={K} kind={kind} B={B} norm={norm}", flush=True)
+    rng = np.random.default_rng(B + K)
+    cap, n, act = 900, 1300, 70  # the ring wraps; more scalar units than a wavefront has lanes
+    row = int(np.prod(shape))
+    done = (rng.random(n) < 0.1).astype(np.uint8)
+    episode, step = synth.episodes_from_done(done)
+    obs = rng.integers(0, 256, (n, row), dtype=np.uint8)
+    reward = rng.standard_normal(n).astype(np.float32)
+    action = rng.integers(0, 256, (n, act), dtype=np.uint8)
+    prio = synth.quantise_priority(rng.lognormal(0, 1, n))
+    buf = cd.ReplayBuffer(cap, shape, torch.uint8, frame_stack=K, action_bytes=act, weight_norm=norm)
+    store = np.zeros((cap, row), np.uint8)
+    orc = oracle.Replay(cap, shape, np.uint8, act_bytes=act, frame_stack=K, obs_storage=store)
+    for a, b in ((0, 700), (700, n)):
+        buf.ingest(dev(obs[a:b].reshape((b - a,) + shape)), action=dev(action[a:b]), reward=dev(reward[a:b]),
+                   done=dev(done[a:b]), episode_id=dev(episode[a:b]), step=dev(step[a:b]), prio=dev(prio[a:b]))
+        orc.ingest(b - a, obs=obs[a:b], action=action[a:b], reward=reward[a:b], done=done[a:b], episode=episode[a:b],
+                   step=step[a:b], prio=prio[a:b])
+    planes = shape[0]
+    xf = cd.transform(kind, MEAN[:planes], STD[:planes]) if kind == cd.XF_U8_BF16_NORM else cd.transform(kind)
+    new = lambda: torch.full((B, K) + shape, 7, dtype=XF_OUT[kind], device="cuda")  # noqa: E731
+    bits = lambda x: np.ascontiguousarray(x).reshape(-1).view(np.uint8)  # noqa: E731
+    for nstep in (0, 3, 0):
+        u = synth.uniforms(rng, B)
+        out, nxt = new(), new()
+        o_act = torch.zeros((B, act), dtype=torch.uint8, device="cuda")
+        o_rew, o_done = torch.zeros(B, device="cuda"), torch.zeros(B, dtype=torch.uint8, device="cuda")
+        o_idx, o_w = orc.sample(u, buffer_norm=bool(norm))
+        if nstep:
+            idx, w, ni, ret, disc, valid = buf.sample_gather_nstep(dev(u), xf, nstep, 0.9, next_obs=nxt, obs=out,
+                                                                   action=o_act, reward=o_rew, done=o_done)
+            want = orc.nstep(o_idx, nstep, 0.9)
+            assert np.array_equal(host(ni), want[0])
+            assert np.allclose(host(ret), want[1], rtol=2.0 ** -23, atol=0)  # fp64 sums rounded to fp32 once
+            assert np.array_equal(host(valid), want[3])
+            has = np.flatnonzero(want[0] >= 0)
+            stacks = orc.gather(want[0][has], kind, MEAN[:planes], STD[:planes])[0]
+            assert np.array_equal(bits(host(nxt)[has]), bits(stacks))
+            assert not host(nxt)[want[0] < 0].any()
+        else:
+            idx, w = buf.sample_gather(dev(u), xf, obs=out, action=o_act, reward=o_rew, done=o_done)
+        assert np.array_equal(host(idx), o_idx)
+        assert_weights_close(host(w), o_w)
+        w_obs, w_act, w_rew, w_done = orc.gather(o_idx, kind, MEAN[:planes], STD[:planes])
+        assert np.array_equal(bits(host(out)), bits(w_obs))
+        assert np.array_equal(host(o_act).reshape(w_act.shape), w_act)
+        assert np.array_equal(host(o_rew), w_rew) and np.array_equal(host(o_done), w_done)
+        idx2, w2 = buf.sample(dev(u))
+        assert np.array_equal(host(idx2), o_idx)
+        assert_weights_close(host(w2), o_w)
+    assert buf.sync_check() == cd.OK, cd.last_error()
     buf.close()

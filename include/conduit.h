@@ -441,8 +441,10 @@ conduit_status conduit_sample_pack_gae(conduit_buffer* buf, int64_t batch, const
  * outputs, which must not overlap the inputs.  Arithmetic in fp64 inside, fp32
  * out.
  * A workgroup takes 32 environments of a rollout of at most 64 steps on its
- * own; longer rollouts are split along T across workgroups, in tiles of 32
- * environments (any E and any 4-byte aligned rows; 16-byte aligned rows with
+ * own (of at most 128 steps from 32 environments on, and of at most 256 steps
+ * from 4,065 on; a wavefront takes 32 or 16 environments of one of at most 16
+ * or 32 steps); longer rollouts are split along T across workgroups, in tiles
+ * of 32 environments (any E and any 4-byte aligned rows; 16-byte aligned rows with
  * E a multiple of 4 take aligned vector accesses, the others 16-byte accesses
  * at 4-byte alignment): up
  * to 4,096 tiles publish their segments' affine maps in a small per-GPU table
@@ -505,8 +507,10 @@ conduit_status conduit_gae_truncated(const float* rewards, const float* values, 
  * steps and E environments whose rows are all 16-byte aligned (aligned != 0)
  * or not, as chosen by the call itself: *path = 0 one workgroup per 8
  * environments walks all T steps, one environment per lane; 1 the same with
- * four environments per lane (E % 4 == 0, aligned); 2 one tile of 32
- * environments per workgroup (T <= 64); 3 split along T, one launch with a
+ * four environments per lane (E % 4 == 0, aligned); 2 one tile per wavefront
+ * or workgroup holds all T steps (T <= 64; T <= 128 with at least 32
+ * environments, T <= 256 with at least 4,065, where path 3 would need no more
+ * than 4,096 tiles); 3 split along T, one launch with a
  * look-back over the later segments' maps (up to 4,096 tiles); 4 split along
  * T in three launches.  Paths 2-4 take any E and either alignment; paths 0
  * and 1 serve only rollouts that need more than 4,096 tiles and have at least

@@ -10,8 +10,8 @@
 //   3. replays each chunk from that carry and writes A_t and R_t = A_t + V_t.
 // All arithmetic is fp64; outputs are rounded to fp32 once.  plan_gae picks
 // the kernels of a time-major call:
-//   * tiles of 32 environments x 32 chunks: a rollout of at most 64 steps is
-//     one tile per workgroup (k_gae_look with one segment); a longer one is
+//   * tiles of 32 environments x 32 chunks: a short rollout is one tile per
+//     workgroup, or per wavefront up to 32 steps (k_gae_tile); a longer one is
 //     split along T into segments whose maps are joined by a decoupled
 //     look-back in one launch (k_gae_look), or, beyond its table, by three
 //     launches (k_gae_seg_*).  With E a multiple of 4 and aligned rows a lane
@@ -28,6 +28,7 @@
 #include <atomic>
 
 #include <mutex>
+#include <type_traits>
 
 #include "common.h"
 #include "gae_plan.h"
@@ -527,13 +528,13 @@ struct SegChunk {
     f32x4 fv[TRUNC ? L : 1];
     f32x4 ve;
 
-    // c: the lane's chunk in the tile.  The value after the chunk's last step
-    // (ve) is the next chunk's first value, which the next lane of the DPP row
-    // loads anyway; the lane loads it itself only in a wavefront's last chunk
-    // (c % 8 == 7) and past the rollout's end (the bootstrap).
-    __device__ __forceinline__ void load(const GaeArgs& a, int64_t t0, int64_t e0, int c) {
+    // The value after the chunk's last step (ve) is the next chunk's first value,
+    // which the next lane of the DPP row loads anyway; the lane loads it itself
+    // only for its quad's last chunk of the wavefront (last) and past the
+    // rollout's end (the bootstrap).
+    __device__ __forceinline__ void load(const GaeArgs& a, int64_t t0, int64_t e0, bool last) {
         const int64_t E = a.E, T = a.T;
-        const bool own = c % kChunksPerWave == kChunksPerWave - 1 || t0 + L >= T;
+        const bool own = last || t0 + L >= T;
         ve = (f32x4)(0.0f);
         if constexpr (V4) {
 #pragma unroll
@@ -738,7 +739,7 @@ __global__ __launch_bounds__(kSegThreads) void k_gae_seg_fold(GaeArgs a, int32_t
     const int64_t e0 = quad_base<V4>(e_raw, E);
     const int64_t t0 = s * Ts + (int64_t)c * L;
     SegChunk<TRUNC, L, V4> ch;
-    ch.load(a, t0, e0, c);
+    ch.load(a, t0, e0, c % kChunksPerWave == kChunksPerWave - 1);
     const Map4 own = ch.fold(a, a.gamma * a.lambda, t0);
     Map4 incl, excl;
     tile_suffix(own, c, q, &incl, &excl);
@@ -837,7 +838,7 @@ __global__ __launch_bounds__(kSegThreads) void k_gae_seg_replay(GaeArgs a, int32
         chi = get_words<V4>(a.adv, row0 + 1, E, e0);
     }
     SegChunk<TRUNC, L, V4> ch;
-    ch.load(a, t0, e0, c);
+    ch.load(a, t0, e0, c % kChunksPerWave == kChunksPerWave - 1);
     const double gl = a.gamma * a.lambda;
     const Map4 own = ch.fold(a, gl, t0);
     double cin[kV];
@@ -888,8 +889,7 @@ __global__ __launch_bounds__(kSegThreads) void k_gae_seg_replay(GaeArgs a, int32
 //   4. publishes A at its own first step when the rollout is longer than one
 //      window (so that look-backs of earlier tiles stop early), then replays its
 //      chunks from the carry.
-// A rollout of one segment (at most 64 steps) skips steps 2 to 4: each tile
-// folds, scans and replays its 32 environments alone.
+// A rollout of one segment takes k_gae_tile instead.
 // Maps and flags live in a small per-GPU table (static device memory, no
 // allocation).  A flag holds the call's epoch next to its state, and every
 // call takes a new epoch on the host, so nothing an earlier call left in the
@@ -930,6 +930,58 @@ __device__ __forceinline__ double get_f64(uint64_t* p) {
     return __longlong_as_double((long long)__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 
+// Replays one lane's chunk from A (at its end) and stores A_t and R_t.  The
+// rows leave without staying dirty in the L2s for the end-of-kernel write-back:
+// through write-through buffer stores at agent scope (8.9 -> 8.7 us on
+// [2048, 256]) where the byte offsets fit a buffer store and the outputs are
+// below kGaeStreamElems each, non-temporally beyond ([4096, 2048] 45.5 -> 40.6
+// us, [256, 32768] truncated 53 -> 49 us; [256, 16384] 18.3 -> 19.0 us).
+constexpr int64_t kGaeStreamElems = 8ll << 20;
+
+template <bool TRUNC, int L, bool V4>
+__device__ __forceinline__ void replay(const GaeArgs& a, const SegChunk<TRUNC, L, V4>& ch, double (&A)[kV], double gl,
+                                       int64_t t0, int64_t e0, bool active) {
+    const int64_t T = a.T, E = a.E;
+    const bool wt = T * E < kGaeStreamElems;  // uniform
+    const int nrec = wt ? (int)(T * E * 4) : 0;
+    const __amdgpu_buffer_rsrc_t rsa = __builtin_amdgcn_make_buffer_rsrc(a.adv, 0, nrec, kRsrcRaw32);
+    const __amdgpu_buffer_rsrc_t rsr = __builtin_amdgcn_make_buffer_rsrc(a.ret, 0, nrec, kRsrcRaw32);
+    double vn[kV];
+#pragma unroll
+    for (int j = 0; j < kV; ++j) vn[j] = (double)ch.ve[j];
+#pragma unroll
+    for (int k = L - 1; k >= 0; --k) {
+        if (t0 + k < T) {
+            f32x4 ao, ro;
+#pragma unroll
+            for (int j = 0; j < kV; ++j) {
+                double delta, m;
+                ch.step(a, gl, k, j, vn[j], &delta, &m);
+                A[j] = delta + m * A[j];
+                ao[j] = (float)A[j];
+                ro[j] = (float)(A[j] + (double)ch.v[k][j]);
+                vn[j] = (double)ch.v[k][j];
+            }
+            if constexpr (V4) {
+                if (!active) continue;
+                const int64_t o = (t0 + k) * E + e0;
+                if (wt) {
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, ao), rsa, (int)(o * 4), 0,
+                                                           kAgentScopeStore);
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, ro), rsr, (int)(o * 4), 0,
+                                                           kAgentScopeStore);
+                } else {
+                    __builtin_nontemporal_store(ao, reinterpret_cast<f32x4*>(a.adv + o));
+                    __builtin_nontemporal_store(ro, reinterpret_cast<f32x4*>(a.ret + o));
+                }
+            } else {
+                put_quad<V4>(a.adv, t0 + k, E, e0, active, ao);
+                put_quad<V4>(a.ret, t0 + k, E, e0, active, ro);
+            }
+        }
+    }
+}
+
 template <bool TRUNC, int L, bool V4>
 __global__ __launch_bounds__(kSegThreads) void k_gae_look(GaeArgs a, LookTable* tab, int32_t groups, int32_t S,
                                                            uint64_t epoch) {
@@ -940,19 +992,19 @@ __global__ __launch_bounds__(kSegThreads) void k_gae_look(GaeArgs a, LookTable* 
     const int64_t s = S - 1 - (int64_t)(blockIdx.x / (uint32_t)groups);  // later segments first
     const int64_t g = blockIdx.x % (uint32_t)groups;
     const int64_t me = s * groups + g;  // table row of this tile
-    const int64_t E = a.E, T = a.T;
+    const int64_t E = a.E;
     const int64_t e_raw = g * kSegEnvs + q * kV;
     const bool active = e_raw < E;
     const int64_t e0 = quad_base<V4>(e_raw, E);
     const int64_t t0 = s * Ts + (int64_t)c * L;
     const double gl = a.gamma * a.lambda;
     SegChunk<TRUNC, L, V4> ch;
-    ch.load(a, t0, e0, c);
+    ch.load(a, t0, e0, c % kChunksPerWave == kChunksPerWave - 1);
     const Map4 own = ch.fold(a, gl, t0);
     Map4 incl, excl;
     tile_suffix(own, c, q, &incl, &excl);  // incl of chunk 0: the segment's map
     const bool last = s == S - 1;
-    if (c == 0 && S > 1) {  // lanes 0..7 of wavefront 0, one per quad; one segment publishes nothing
+    if (c == 0) {  // lanes 0..7 of wavefront 0, one per quad
 #pragma unroll
         for (int j = 0; j < kV; ++j) {
             if (last) {
@@ -1030,44 +1082,58 @@ __global__ __launch_bounds__(kSegThreads) void k_gae_look(GaeArgs a, LookTable* 
         for (int j = 0; j < kV; ++j) s_cin[q][j] = 0.0;  // A_T = 0
     }
     __syncthreads();
-    // A and R leave through write-through buffer stores at agent scope (no
-    // dirty lines for the end-of-kernel write-back: 8.9 -> 8.7 us on
-    // [2048, 256]) where the byte offsets fit a buffer store
-    const bool wt = T * E * 4 <= 0x7fffffffll;  // uniform
-    const int nrec = wt ? (int)(T * E * 4) : 0;
-    const __amdgpu_buffer_rsrc_t rsa = __builtin_amdgcn_make_buffer_rsrc(a.adv, 0, nrec, kRsrcRaw32);
-    const __amdgpu_buffer_rsrc_t rsr = __builtin_amdgcn_make_buffer_rsrc(a.ret, 0, nrec, kRsrcRaw32);
-    double A[kV], vn[kV];
+    double A[kV];
 #pragma unroll
-    for (int j = 0; j < kV; ++j) {
-        A[j] = excl.P[j] * s_cin[q][j] + excl.S[j];  // A at the end of this chunk
-        vn[j] = (double)ch.ve[j];
+    for (int j = 0; j < kV; ++j) A[j] = excl.P[j] * s_cin[q][j] + excl.S[j];  // A at the end of this chunk
+    replay<TRUNC, L, V4>(a, ch, A, gl, t0, e0, active);
+}
+
+// Rollouts of one segment: a tile holds all T steps, so no tile waits for
+// another.  A quad's chunks are CW neighbouring lanes of a wavefront, and WT
+// wavefronts (1, or 4 with an LDS exchange) make a tile of CW * WT chunks: 16
+// steps of 32 environments, or 32 of 16, per wavefront, 64, 128 or 256 of 32 per
+// workgroup.  Bound by the loads' latency for few environments and by HBM for
+// many.  The look-back's registers (270 with truncation at L = 4: one workgroup
+// per compute unit) are not needed here.
+template <bool TRUNC, int L, bool V4, int CW, int WT>
+__global__ __launch_bounds__(kSegThreads) void k_gae_tile(GaeArgs a) {
+    static_assert(WT == 1 || (WT == kSegWaves && CW == kChunksPerWave), "a wavefront or a workgroup per tile");
+    const int lane = (int)threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    const int q = lane / CW, cw = lane % CW;
+    const int64_t tile = WT == 1 ? (int64_t)blockIdx.x * kSegWaves + wave : (int64_t)blockIdx.x;
+    const int64_t e_raw = (tile * (kWave / CW) + q) * kV;
+    const int64_t E = a.E;
+    if (WT == 1 && tile * (kWave / CW) * kV >= E) return;  // a whole wavefront past the last environment
+    const bool active = e_raw < E;
+    const int64_t e0 = quad_base<V4>(e_raw, E);
+    const int c = WT == 1 ? cw : wave * CW + cw;
+    const int64_t t0 = (int64_t)c * L;
+    const double gl = a.gamma * a.lambda;
+    SegChunk<TRUNC, L, V4> ch;
+    ch.load(a, t0, e0, cw == CW - 1);
+    const Map4 own = ch.fold(a, gl, t0);
+    double A[kV];  // at the end of this chunk: the later chunks' maps applied to A_T = 0
+    if constexpr (WT == 1) {
+        Map4 in = own;
+        auto step = [&](auto n) {
+            const Map4 nx = map_from_lane_up<n.value>(in);
+            if (cw + n.value < CW) in = map_compose(in, nx);
+        };
+        step(std::integral_constant<int, 1>{});
+        step(std::integral_constant<int, 2>{});
+        step(std::integral_constant<int, 4>{});
+        if constexpr (CW == 16) step(std::integral_constant<int, 8>{});
+        const Map4 ex = map_from_lane_up<1>(in);
+#pragma unroll
+        for (int j = 0; j < kV; ++j) A[j] = cw == CW - 1 ? 0.0 : ex.S[j];
+    } else {
+        Map4 incl, excl;
+        tile_suffix(own, c, q, &incl, &excl);
+#pragma unroll
+        for (int j = 0; j < kV; ++j) A[j] = excl.S[j];
     }
-#pragma unroll
-    for (int k = L - 1; k >= 0; --k) {
-        if (t0 + k < T) {
-            f32x4 ao, ro;
-#pragma unroll
-            for (int j = 0; j < kV; ++j) {
-                double delta, m;
-                ch.step(a, gl, k, j, vn[j], &delta, &m);
-                A[j] = delta + m * A[j];
-                ao[j] = (float)A[j];
-                ro[j] = (float)(A[j] + (double)ch.v[k][j]);
-                vn[j] = (double)ch.v[k][j];
-            }
-            if (V4 && wt) {
-                if (active) {
-                    const int off = (int)(((t0 + k) * E + e0) * 4);
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, ao), rsa, off, 0, kAgentScopeStore);
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, ro), rsr, off, 0, kAgentScopeStore);
-                }
-            } else {
-                put_quad<V4>(a.adv, t0 + k, E, e0, active, ao);
-                put_quad<V4>(a.ret, t0 + k, E, e0, active, ro);
-            }
-        }
-    }
+    replay<TRUNC, L, V4>(a, ch, A, gl, t0, e0, active);
 }
 
 __global__ __launch_bounds__(kPkThreads) void k_gae_packed(GaePackedArgs a) {
@@ -1134,6 +1200,23 @@ hipError_t launch_gae_look_l(const GaeArgs& a, LookTable* tab, int32_t groups, i
     return hipGetLastError();
 }
 
+template <bool TRUNC, bool V4>
+hipError_t launch_gae_tile_l(const GaeArgs& a, int L, hipStream_t s) {
+    const dim3 block(kSegThreads);
+    auto tiles = [&](int64_t envs) { return dim3((unsigned)((a.E + envs - 1) / envs)); };
+    if (L == 8) hipLaunchKernelGGL((k_gae_tile<TRUNC, 8, V4, 8, 4>), tiles(kSegEnvs), block, 0, s, a);
+    else if (L == 4) hipLaunchKernelGGL((k_gae_tile<TRUNC, 4, V4, 8, 4>), tiles(kSegEnvs), block, 0, s, a);
+    else if (a.T <= 16) hipLaunchKernelGGL((k_gae_tile<TRUNC, 2, V4, 8, 1>), tiles(4 * 32), block, 0, s, a);
+    else if (a.T <= 32) hipLaunchKernelGGL((k_gae_tile<TRUNC, 2, V4, 16, 1>), tiles(4 * 16), block, 0, s, a);
+    else hipLaunchKernelGGL((k_gae_tile<TRUNC, 2, V4, 8, 4>), tiles(kSegEnvs), block, 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_gae_tile(const GaeArgs& a, int L, bool v4, hipStream_t s) {
+    if (v4) return a.truncated ? launch_gae_tile_l<true, true>(a, L, s) : launch_gae_tile_l<false, true>(a, L, s);
+    return a.truncated ? launch_gae_tile_l<true, false>(a, L, s) : launch_gae_tile_l<false, false>(a, L, s);
+}
+
 std::atomic<uint64_t> g_look_epoch{0};  // epochs of the look-back table, 1, 2, ... (62 bits)
 
 // Device address of the current GPU's table, found once per GPU (with that GPU
@@ -1159,9 +1242,8 @@ static hipError_t gae_table(LookTable** out) {
 }
 
 hipError_t launch_gae_look(const GaeArgs& a, int32_t groups, int32_t S, int L, bool v4, hipStream_t s) {
-    // one segment (the short path) uses no table; split rollouts at most the
-    // table's tiles (the plan never asks for more)
-    if (S > 1 && (int64_t)groups * S > kLookMaxTiles) return hipErrorInvalidValue;
+    // at most the table's tiles (the plan never asks for more)
+    if ((int64_t)groups * S > kLookMaxTiles) return hipErrorInvalidValue;
     LookTable* tab = nullptr;
     hipError_t e = gae_table(&tab);
     if (e != hipSuccess) return e;
@@ -1169,7 +1251,7 @@ hipError_t launch_gae_look(const GaeArgs& a, int32_t groups, int32_t S, int L, b
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     e = hipStreamIsCapturing(s, &cap);
     if (e != hipSuccess) return e;
-    if (S > 1 && cap != hipStreamCaptureStatusNone) {  // replays repeat the epoch: clear the flags first
+    if (cap != hipStreamCaptureStatusNone) {  // replays repeat the epoch: clear the flags first
         hipLaunchKernelGGL(k_gae_look_clear, dim3(1), dim3(kSegThreads), 0, s, tab, groups * S);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -1241,7 +1323,15 @@ GaePlan plan_gae(int64_t T, int64_t E, bool vec) {
     if (L == 8 && groups * segs_of(4) >= kGaeSplitManyTiles && groups * segs_of(4) <= kLookMaxTiles) L = 4;
     if (!L) return p;
     const int64_t segs = segs_of(L);
-    if (groups * segs <= kLookMaxTiles) return GaePlan{GAE_LOOK_BACK, L, groups, segs};
+    if (groups * segs <= kLookMaxTiles) {
+        // one segment of longer chunks spares the look-back: up to 128 steps for
+        // every whole group of environments ([128, 64] 5.8 -> 5.0 us, [128, 4096]
+        // 7.2 -> 5.8, [128, 16384] 13.9 -> 9.4), up to 256 where half the compute
+        // units get a tile ([256, 4096] 9.3 -> 8.7, [256, 1024] 7.2 -> 7.9)
+        if (T <= (int64_t)kSegChunks * 4 && E >= kSegEnvs) return GaePlan{GAE_SHORT, 4, groups, 1};
+        if (T <= (int64_t)kSegChunks * 8 && groups >= kGaeSplitMinTiles / 2) return GaePlan{GAE_SHORT, 8, groups, 1};
+        return GaePlan{GAE_LOOK_BACK, L, groups, segs};
+    }
     // beyond the table: three launches for narrow rollouts; wide ones keep one
     // workgroup per 8 environments, which already fills the GPU
     if (E < kGaeSplitMaxEnvs) return GaePlan{GAE_THREE_LAUNCHES, L, groups, segs};
@@ -1257,7 +1347,7 @@ hipError_t launch_gae(const GaeArgs& a, hipStream_t s) {
                      al(a.final_value, 16);
     const GaePlan p = plan_gae(a.T, a.E, vec);
     switch (p.path) {
-        case GAE_SHORT:
+        case GAE_SHORT: return launch_gae_tile(a, p.chunk, vec, s);
         case GAE_LOOK_BACK: return launch_gae_look(a, (int32_t)p.groups, (int32_t)p.segments, p.chunk, vec, s);
         case GAE_THREE_LAUNCHES: return launch_gae_split(a, p.groups, p.chunk, vec, s);
         case GAE_ONE_PASS_V4: {

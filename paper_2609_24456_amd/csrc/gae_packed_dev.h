@@ -1,6 +1,6 @@
 // Generalised advantage estimation over packed (right-padded) sequences, one
-// workgroup per sequence: shared by the packed GAE kernel (512 lanes) and the
-// fused sampler + packing + GAE kernel (its pack workgroup as it is).
+// workgroup per sequence: shared by the packed GAE kernel and the fused sampler +
+// packing + GAE kernel (its pack workgroup as it is).
 #pragma once
 #include "common.h"
 
@@ -12,22 +12,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kRsrcRaw32 = 0x00020000;  // raw buffer descriptor, 32-bit data format
 constexpr int kAgentScopeStore = 16;    // cache policy SC1: written through at agent scope
 
-// Lanes of the stand-alone packed GAE kernel.  A sequence of 4,096 elements
-// as 512 lanes x 8 (against 256 x 16): [256, 4096] 6.9 -> 5.5 us, [1024, 4096]
-// 13.2 -> 11.8 us, [256, 1024] 6.0 -> 4.7 us; 1,024 lanes x 4 gains at 256
-// rows (5.9 us) but loses at 1,024 (18.7 us).
-constexpr int kPkThreads = 512;
-constexpr int kPkSeg = 4096;                      // elements per pass
-constexpr int kPkPad = kPkSeg + kPkSeg / 16 + 1;  // padded LDS row
-
-// padded LDS index: one spare word every 16, so lanes reading their own
-// contiguous chunk of up to 16 hit distinct banks
-__device__ __forceinline__ int lpad(int t) { return t + (t >> 4); }
-
-// GAE over right-padded sequences, one workgroup per sequence, walked in
-// segments of 4096 elements from the end with a carry.  Values are staged into
-// LDS with coalesced loads, each lane owns a contiguous chunk of 16 for the scan,
-// and advantages/returns are staged back and written coalesced.
 // A double moved by one DPP control; lanes with no source keep `id`.
 template <int CTRL, int ROWS>
 __device__ __forceinline__ double dpp_f64(double x, double id) {
@@ -110,181 +94,227 @@ __device__ void gae_packed_row_novalue(const GaePackedArgs& a, int64_t b, int64_
     }
 }
 
+// 16 bytes at a 4-byte aligned address
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// Powers of gamma lambda for the scan of a block whose lanes all have the same
+// map, A_start = (gamma lambda)^4 A_end + S: only the S parts move then.
+struct LanePowers {
+    double p1, p2, p4, p8;  // of 1, 2, 4, 8 lanes
+    double row, half;       // of the lanes up to this one in its row of 16, its half of 32
+    double later, block;    // of the lanes before this one (later in time), of all 64
+    __device__ __forceinline__ LanePowers(double gl, int lane) {
+        p1 = (gl * gl) * (gl * gl);
+        p2 = p1 * p1;
+        p4 = p2 * p2;
+        p8 = p4 * p4;
+        const double p16 = p8 * p8, p32 = p16 * p16;
+        const double in_row = ((lane & 1) ? p1 : 1.0) * ((lane & 2) ? p2 : 1.0) * ((lane & 4) ? p4 : 1.0) *
+                              ((lane & 8) ? p8 : 1.0);
+        const double in_half = in_row * ((lane & 16) ? p16 : 1.0);
+        row = in_row * p1;
+        half = in_half * p1;
+        later = in_half * ((lane & 32) ? p32 : 1.0);
+        block = p32 * p32;
+    }
+};
+
 // GAE of packed row b, of L live elements (0 <= L <= Lmax) with reward R on
-// the last one, by one workgroup of NT lanes (each lane a chunk of 4096 / NT
-// consecutive elements per pass).
-template <int NT>
+// the last one, by one workgroup of NT lanes, in passes of 4 NT J elements from
+// the row's end.  A wavefront owns 256 J consecutive elements of a pass, as J
+// blocks of one 16-byte vector per lane, so values and outputs stay in registers
+// and every access is contiguous over the wavefront.  Lanes run backwards in
+// time (lane 0 holds a block's last vector), so the suffix composition of the
+// lanes' affine maps is a DPP prefix scan; the blocks' maps compose in scalar
+// order, the wavefronts' through LDS with one barrier per pass.  A block that
+// ends before the sequence's last element has the same coefficient everywhere,
+// so only the S parts of its maps are scanned (LanePowers): the fp64 arithmetic
+// bounds the kernel as much as the chain of its latencies does.  The next pass's
+// values load before the current one is worked on; padding is not read.
+// Against staging each row through LDS, 4,096 elements at a time: [256, 8192] 9.3
+// -> 8.0 us, [244, 16384] 16.0 -> 11.4, rows off 16 bytes [244, 16383] 23.0 ->
+// 11.2, [1024, 1024] 10.2 -> 5.8, [1024, 4096] 14.0 -> 11.8; the fused sample +
+// pack + GAE of [1024, 1024] 21.3 -> 19.2.
+template <int NT, int J>
 __device__ void gae_packed_row(const GaePackedArgs& a, int64_t b, int64_t L, double R) {
     if (!a.value) {  // kernel argument: uniform
         gae_packed_row_novalue<NT>(a, b, L, R);
         return;
     }
-    static_assert(NT % kWave == 0 && kPkSeg % (4 * NT) == 0 && kPkSeg / NT <= 16, "lanes per sequence");
-    constexpr int kPkChunk = kPkSeg / NT;  // elements per lane and pass
-    __shared__ float sV[kPkPad];
-    __shared__ float sA[kPkPad];
-    __shared__ float sR[kPkPad];
-    __shared__ double sWP[NT / kWave];
-    __shared__ double sWS[NT / kWave];
-    const int tid = threadIdx.x;
-    // chunks run backwards inside a wavefront (lane 0 holds its last chunk), so
-    // the suffix composition over the chunks is a prefix scan over the lanes
-    const int wv = tid / kWave, lane = tid % kWave;
-    const int c = wv * kWave + (kWave - 1 - lane);
+    constexpr int kWaves = NT / kWave;
+    constexpr int64_t kWaveSpan = 4 * kWave * J;  // elements of a wavefront and pass
+    constexpr int64_t kPass = kWaveSpan * kWaves;
+    __shared__ double sWP[2][kWaves], sWS[2][kWaves];
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), lane = lane_id();
     const int64_t Lmax = a.Lmax;
-    const float* val = a.value ? a.value + b * Lmax : nullptr;
+    const float* __restrict__ val = a.value + b * Lmax;
     float* adv = a.adv + b * Lmax;
     float* ret = a.ret + b * Lmax;
-    // 16-byte vectors for the value loads and the output stores when the rows
-    // allow them (uniform)
-    auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-    const bool vec_in = val && al16(val);
-    const bool vec_out = al16(adv) && al16(ret);
     const double gl = a.gamma * a.lambda;
-    double carry = 0.0;    // A at the start of the later segment
-    double v_after = 0.0;  // V at the start of the later segment
-    const int64_t segs = (Lmax + kPkSeg - 1) / kPkSeg;
-    for (int64_t sg = segs - 1; sg >= 0; --sg) {
-        const int64_t base = sg * kPkSeg;
-        const int seg_len = (int)(Lmax - base < kPkSeg ? Lmax - base : kPkSeg);
-        if (vec_in) {
-            // every lane's 4 vectors are loaded before the first LDS write
-            constexpr int kVecs = kPkSeg / (4 * NT);
-            f32x4 q[kVecs];
+    const int own = (kWave - 1 - lane) * 4;  // the lane's vector in a block
+    // the lane's vectors of the pass at `base`, and the value after the
+    // wavefront's span (0 where nothing live lies there)
+    auto load = [&](int64_t base, f32x4 (&v)[J], float& after) {
+        const int64_t w0 = base + wv * kWaveSpan;
 #pragma unroll
-            for (int j = 0; j < kVecs; ++j) {
-                const int t = (j * NT + tid) * 4;
-                if (t + 3 < seg_len) {
-                    q[j] = *reinterpret_cast<const f32x4*>(val + base + t);
+        for (int j = 0; j < J; ++j) {
+            const int64_t t = w0 + j * 4 * kWave + own;
+            v[j] = (f32x4)(0.0f);
+            if (t < L) {
+                if (t + 3 < Lmax) {
+                    v[j] = *reinterpret_cast<const f32x4u*>(val + t);
                 } else {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) q[j][i] = t + i < seg_len ? val[base + t + i] : 0.0f;
+                    for (int i = 0; i < 3; ++i) v[j][i] = t + i < Lmax ? val[t + i] : 0.0f;
                 }
             }
-#pragma unroll
-            for (int j = 0; j < kVecs; ++j) {
-                const int t = (j * NT + tid) * 4;
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (t + i < seg_len) sV[lpad(t + i)] = q[j][i];
-            }
+        }
+        const int64_t e = w0 + kWaveSpan;
+        after = e < L ? val[e] : 0.0f;
+    };
+    auto put = [&](int64_t t, const f32x4& x, const f32x4& y) {
+        if (t + 3 < Lmax) {
+            *reinterpret_cast<f32x4u*>(adv + t) = x;
+            *reinterpret_cast<f32x4u*>(ret + t) = y;
         } else {
-            for (int t = tid; t < seg_len; t += NT) sV[lpad(t)] = val ? val[base + t] : 0.0f;
-        }
-        __syncthreads();
-        // this lane's chunk [t0, t1) of the segment, live part [t0, u1)
-        const int t0 = c * kPkChunk;
-        const int t1 = t0 + kPkChunk < seg_len ? t0 + kPkChunk : seg_len;
-        const int64_t live_end = L - base;
-        const int u1 = (int)(t1 < live_end ? t1 : (live_end > t0 ? live_end : t0));
-        double v_end = 0.0;  // V after the chunk's live part, when the sequence continues
-        if (base + u1 < L && u1 > t0) v_end = u1 < seg_len ? (double)sV[lpad(u1)] : v_after;
-        double P = 1.0, S = 0.0;
-        {
-            double v_next = v_end;
 #pragma unroll
-            for (int k = kPkChunk - 1; k >= 0; --k) {
-                const int t = t0 + k;
-                if (t < u1) {
-                    const double v = (double)sV[lpad(t)];
-                    const bool last = base + t == L - 1;
-                    const double live = last ? 0.0 : 1.0;
-                    const double delta = (last ? R : 0.0) + a.gamma * live * v_next - v;
-                    const double m = gl * live;
-                    S = delta + m * S;
-                    P = m * P;
-                    v_next = v;
+            for (int i = 0; i < 3; ++i) {
+                if (t + i < Lmax) {
+                    adv[t + i] = x[i];
+                    ret[t + i] = y[i];
                 }
             }
         }
-        // suffix composition over the chunks: a DPP prefix scan inside each
-        // wavefront (shifts by 1, 2, 4, 8 in a row, then the row broadcasts),
-        // the wavefront totals through LDS, one barrier
-        double iP = P, iS = S;  // chunks c .. the wavefront's last
-        later_scan_step<kDppRowShr + 1, 0xf>(iP, iS);
-        later_scan_step<kDppRowShr + 2, 0xf>(iP, iS);
-        later_scan_step<kDppRowShr + 4, 0xf>(iP, iS);
-        later_scan_step<kDppRowShr + 8, 0xf>(iP, iS);
-        later_scan_step<kDppRowBcast15, 0xa>(iP, iS);
-        later_scan_step<kDppRowBcast31, 0xc>(iP, iS);
-        const double eP = dpp_f64<kDppWaveShr1, 0xf>(iP, 1.0);  // chunks c + 1 .. the last
-        const double eS = dpp_f64<kDppWaveShr1, 0xf>(iS, 0.0);
-        if (lane == kWave - 1) {
-            sWP[wv] = iP;
-            sWS[wv] = iS;
-        }
-        __syncthreads();
-        double lP = 1.0, lS = 0.0;  // the later wavefronts' chunks
-        double tP = 1.0, tS = 0.0;  // the whole segment
+    };
+    // a block whose elements all come before the sequence's last one
+    auto inside = [&](int64_t b0) { return b0 + 4 * kWave < L; };
+    const LanePowers pw(gl, lane);
+    int64_t base = (Lmax + kPass - 1) / kPass * kPass - kPass;
+    for (; base >= L && base >= 0; base -= kPass) {  // passes of padding only (uniform)
 #pragma unroll
-        for (int w = NT / kWave - 1; w >= 0; --w) {
-            tS = sWS[w] + sWP[w] * tS;
-            tP = sWP[w] * tP;
-            if (w == wv + 1) {
+        for (int j = 0; j < J; ++j) put(base + wv * kWaveSpan + j * 4 * kWave + own, (f32x4)(0.0f), (f32x4)(0.0f));
+    }
+    f32x4 v[J], vn[J];
+    float after = 0.0f, after_n = 0.0f;
+    if (base >= 0) load(base, v, after);
+    double carry = 0.0;  // A at the start of the later pass
+    for (int par = 0; base >= 0; base -= kPass, par ^= 1) {
+        if (base > 0) load(base - kPass, vn, after_n);
+        const int64_t w0 = base + wv * kWaveSpan;
+        double end[J];            // V after the lane's vector
+        double eP[J], eS[J];      // the block's later lanes
+        double bP[J], bS[J];      // the wavefront's later blocks
+        double wP = 1.0, wS = 0.0;
+#pragma unroll
+        for (int j = J - 1; j >= 0; --j) {
+            const int64_t b0 = w0 + j * 4 * kWave, t = b0 + own;
+            bP[j] = wP;
+            bS[j] = wS;
+            eP[j] = 1.0;
+            eS[j] = 0.0;
+            end[j] = 0.0;
+            if (b0 >= L) continue;  // padding only (uniform)
+            const float next = j + 1 < J ? __uint_as_float(__builtin_amdgcn_readlane(
+                                               __float_as_uint(v[j + 1 < J ? j + 1 : j][0]), kWave - 1))
+                                         : after;
+            const float up = __uint_as_float(dpp_u32<kDppWaveShr1, 0xf>(__float_as_uint(v[j][0]), __float_as_uint(next)));
+            double S = 0.0, tP;
+            if (inside(b0)) {  // uniform
+                end[j] = (double)up;
+                double v_next = end[j];
+#pragma unroll
+                for (int i = 3; i >= 0; --i) {
+                    const double x = (double)v[j][i];
+                    S = (a.gamma * v_next - x) + gl * S;
+                    v_next = x;
+                }
+                S += pw.p1 * dpp_f64<kDppRowShr + 1, 0xf>(S, 0.0);
+                S += pw.p2 * dpp_f64<kDppRowShr + 2, 0xf>(S, 0.0);
+                S += pw.p4 * dpp_f64<kDppRowShr + 4, 0xf>(S, 0.0);
+                S += pw.p8 * dpp_f64<kDppRowShr + 8, 0xf>(S, 0.0);
+                S += pw.row * dpp_f64<kDppRowBcast15, 0xa>(S, 0.0);
+                S += pw.half * dpp_f64<kDppRowBcast31, 0xc>(S, 0.0);
+                eP[j] = pw.later;
+                tP = pw.block;
+            } else {
+                end[j] = t + 4 < L ? (double)up : 0.0;  // what lies past the sequence is never used
+                double v_next = end[j];
+                double P = 1.0;
+#pragma unroll
+                for (int i = 3; i >= 0; --i) {
+                    if (t + i < L) {
+                        const double x = (double)v[j][i];
+                        const bool last = t + i == L - 1;
+                        S = last ? R - x : (a.gamma * v_next - x) + gl * S;
+                        P = last ? 0.0 : gl * P;
+                        v_next = x;
+                    }
+                }
+                // shifts by 1, 2, 4, 8 in a row, then the row broadcasts
+                later_scan_step<kDppRowShr + 1, 0xf>(P, S);
+                later_scan_step<kDppRowShr + 2, 0xf>(P, S);
+                later_scan_step<kDppRowShr + 4, 0xf>(P, S);
+                later_scan_step<kDppRowShr + 8, 0xf>(P, S);
+                later_scan_step<kDppRowBcast15, 0xa>(P, S);
+                later_scan_step<kDppRowBcast31, 0xc>(P, S);
+                eP[j] = dpp_f64<kDppWaveShr1, 0xf>(P, 1.0);
+                tP = __longlong_as_double((long long)readlane_u64((uint64_t)__double_as_longlong(P), kWave - 1));
+            }
+            eS[j] = dpp_f64<kDppWaveShr1, 0xf>(S, 0.0);
+            const double tS = __longlong_as_double((long long)readlane_u64((uint64_t)__double_as_longlong(S), kWave - 1));
+            wS = tS + tP * wS;
+            wP = tP * wP;
+        }
+        if (lane == 0) {
+            sWP[par][wv] = wP;
+            sWS[par][wv] = wS;
+        }
+        lds_barrier();  // the pass before used the other half
+        double lP = 1.0, lS = 0.0;  // the later wavefronts
+        double tP = 1.0, tS = 0.0;  // the whole pass
+#pragma unroll
+        for (int w = kWaves - 1; w >= 0; --w) {
+            if (w == wv) {
                 lP = tP;
                 lS = tS;
             }
+            tS = sWS[par][w] + sWP[par][w] * tS;
+            tP = sWP[par][w] * tP;
         }
-        double A = eP * (lP * carry + lS) + eS;  // A at the end of this chunk
-        {
-            double v_next = v_end;
+        const double A_w = lP * carry + lS;  // A at the end of the wavefront's span
 #pragma unroll
-            for (int k = kPkChunk - 1; k >= 0; --k) {
-                const int t = t0 + k;
-                if (t < t1) {
-                    if (t < u1) {
-                        const double v = (double)sV[lpad(t)];
-                        const bool last = base + t == L - 1;
-                        const double live = last ? 0.0 : 1.0;
-                        const double delta = (last ? R : 0.0) + a.gamma * live * v_next - v;
-                        A = delta + gl * live * A;
-                        sA[lpad(t)] = (float)A;
-                        sR[lpad(t)] = (float)(A + v);
-                        v_next = v;
-                    } else {
-                        sA[lpad(t)] = 0.0f;
-                        sR[lpad(t)] = 0.0f;
+        for (int j = J - 1; j >= 0; --j) {
+            const int64_t b0 = w0 + j * 4 * kWave, t = b0 + own;
+            double A = eP[j] * (bP[j] * A_w + bS[j]) + eS[j];
+            double v_next = end[j];
+            f32x4 oa = (f32x4)(0.0f), orr = (f32x4)(0.0f);
+            if (inside(b0)) {
+#pragma unroll
+                for (int i = 3; i >= 0; --i) {
+                    const double x = (double)v[j][i];
+                    A = (a.gamma * v_next - x) + gl * A;
+                    oa[i] = (float)A;
+                    orr[i] = (float)(A + x);
+                    v_next = x;
+                }
+            } else if (b0 < L) {
+#pragma unroll
+                for (int i = 3; i >= 0; --i) {
+                    if (t + i < L) {
+                        const double x = (double)v[j][i];
+                        A = t + i == L - 1 ? R - x : (a.gamma * v_next - x) + gl * A;
+                        oa[i] = (float)A;
+                        orr[i] = (float)(A + x);
+                        v_next = x;
                     }
                 }
             }
-        }
-        __syncthreads();
-        if (vec_out) {
-            constexpr int kVecs = kPkSeg / (4 * NT);
-            // write-through buffer stores at agent scope over this segment (the
-            // rows leave no dirty lines for the end-of-kernel write-back: 7.95
-            // -> 7.26 us for [256, 4096], the tokens iteration 22.7 -> 22.0 us)
-            const int nb = __builtin_amdgcn_readfirstlane(seg_len * 4);
-            const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(adv + base, 0, nb, kRsrcRaw32);
-            const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(ret + base, 0, nb, kRsrcRaw32);
-#pragma unroll
-            for (int j = 0; j < kVecs; ++j) {
-                const int t = (j * NT + tid) * 4;
-                if (t + 3 < seg_len) {
-                    f32x4 oa, orr;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        oa[i] = sA[lpad(t + i)];
-                        orr[i] = sR[lpad(t + i)];
-                    }
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, oa), ra, t * 4, 0, kAgentScopeStore);
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, orr), rr, t * 4, 0, kAgentScopeStore);
-                } else {
-                    for (int i = 0; i < 4 && t + i < seg_len; ++i) {
-                        adv[base + t + i] = sA[lpad(t + i)];
-                        ret[base + t + i] = sR[lpad(t + i)];
-                    }
-                }
-            }
-        } else {
-            for (int t = tid; t < seg_len; t += NT) {
-                adv[base + t] = sA[lpad(t)];
-                ret[base + t] = sR[lpad(t)];
-            }
+            put(t, oa, orr);
         }
         carry = tP * carry + tS;
-        v_after = (double)sV[lpad(0)];
-        __syncthreads();  // LDS is rewritten by the next segment
+#pragma unroll
+        for (int j = 0; j < J; ++j) v[j] = vn[j];
+        after = after_n;
     }
 }
 

@@ -380,7 +380,7 @@ __global__ __launch_bounds__(pack_wg<GAE>()) void k_sample_pack(SampleArgs sa, P
     }
     __syncthreads();
     const PackedRow row = pack_row<NT>(pa, b, s_slot);
-    if constexpr (GAE) gae_packed_row<NT>(ga, b, row.L, (double)row.R);
+    if constexpr (GAE) gae_packed_row<NT, 2>(ga, b, row.L, (double)row.R);
 }
 
 struct PackLaunch {

@@ -37,7 +37,8 @@ __global__ __launch_bounds__(kUpdateThreads) void k_update(UpdateArgs a) {
     __shared__ uint32_t keys[kTable];
     __shared__ int32_t owner[kTable];
     __shared__ unsigned long long bins[kBins];
-    const uint32_t seen = a.state->max_prio;
+    // one workgroup's atomics cost less than waiting for the stored maximum
+    const uint32_t seen = SPLIT > 0 ? a.state->max_prio : 0u;
     uint32_t pmax;
     if constexpr (SPLIT > 0) pmax = update_part<SPLIT>(a, blockIdx.x, gridDim.x, keys, owner, bins);
     else pmax = update_pass(a, keys, owner, bins);

@@ -62,7 +62,8 @@ __global__ __launch_bounds__(kUpdateThreads) void k_update_ingest(UpdateArgs u, 
     __shared__ int32_t owner[kTable];
     __shared__ unsigned long long bins[kBins];
     if (blockIdx.x < (uint32_t)groups) {
-        const uint32_t seen = u.state->max_prio;
+        // one workgroup's atomics cost less than waiting for the stored maximum
+        const uint32_t seen = SPLIT > 0 ? u.state->max_prio : 0u;
         uint32_t pmax;
         if constexpr (SPLIT > 0) pmax = update_part<SPLIT>(u, blockIdx.x, (uint32_t)groups, keys, owner, bins, a.head, a.n);
         else pmax = update_pass(u, keys, owner, bins, a.head, a.n);

@@ -15,6 +15,7 @@ __device__ __forceinline__ uint32_t slot_hash(uint32_t key) { return (key * 0x9E
 
 // whether an ingest of ring slots [ev_head, ev_head + ev_n) replaces `slot`
 __device__ __forceinline__ bool evicted(const TreeView& tr, int64_t slot, int64_t ev_head, int64_t ev_n) {
+    if (ev_n <= 0) return false;  // known when compiled where there is no ingest
     const int64_t back = slot - ev_head;
     return (back < 0 ? back + tr.nodes[0] : back) < ev_n;
 }

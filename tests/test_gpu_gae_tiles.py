@@ -44,3 +44,30 @@ def test_gae_one_tile(T, E, shift, path, chunk, truncated):
         assert cd.conduit_sync_check() == cd.OK, cd.last_error()
         assert_gae_close(host(adv), oa)
         assert_gae_close(host(ret), orr)
+
+
+# packed rows around each width the kernel is dispatched on, rows off 16 bytes,
+# lengths at the edges of a wavefront's blocks and spans and of a pass (padding
+# only, one live element, the whole row), and padding that must not be used
+@pytest.mark.parametrize("Lmax,gamma,lam", [
+    (1, 0.9, 0.8), (255, 1.0, 0.95), (1024, 1.0, 0.95), (1025, 0.99, 1.0), (2048, 1.0, 0.95), (2050, 1.0, 0.5),
+    (4096, 0.0, 0.95), (4100, 1.0, 0.95), (8192, 1.0, 0.999), (8193, 0.99, 0.95), (16387, 1.0, 0.99)])
+def test_gae_packed_widths(Lmax, gamma, lam):
+    print(f"packed Lmax={Lmax}", flush=True)
+    rng = np.random.default_rng(Lmax)
+    edges = [0, 1, 2, 4, 5, 255, 256, 257, 260, 511, 512, 1023, 1024, 1025, 1028, 2047, 2049, 4095, 4096, 4097, 8192, 8193,
+             Lmax - 1, Lmax]
+    length = np.array([x for x in edges if 0 <= x <= Lmax], np.int32)
+    B = len(length)
+    R = rng.standard_normal(B).astype(np.float32)
+    v = rng.standard_normal((B, Lmax)).astype(np.float32)
+    oa, orr = oracle.gae_packed(R, length, v, Lmax, gamma, lam)
+    pad = np.arange(Lmax)[None, :] >= length[:, None]
+    v[pad] = np.nan  # never used
+    adv = torch.full((B, Lmax), np.nan, dtype=torch.float32, device="cuda")
+    ret = torch.full((B, Lmax), np.nan, dtype=torch.float32, device="cuda")
+    cd.conduit_gae_packed(dev(R), dev(length), dev(v), Lmax, gamma, lam, adv, ret)
+    assert cd.conduit_sync_check() == cd.OK, cd.last_error()
+    assert_gae_close(host(adv), oa)
+    assert_gae_close(host(ret), orr)
+    assert not host(adv)[pad].any() and not host(ret)[pad].any()

@@ -33,8 +33,10 @@ def _compile(src, verbose):
 
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+        check = ex.submit(build_tensor_check, verbose)
         objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
+        check.result()
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", LIB + ".tmp"] + objs
     if verbose:
         print(" ".join(cmd), flush=True)
@@ -43,6 +45,32 @@ def build(verbose: bool = False) -> str:
         raise RuntimeError(f"link failed:\n{r.stderr}")
     os.replace(LIB + ".tmp", LIB)
     return LIB
+
+
+# The binding's native argument check (csrc/tensor_check.cpp), a CPython module
+# against the installed torch.
+TENSOR_CHECK = os.path.join(PKG, "_tensor_check.so")
+
+
+def build_tensor_check(verbose: bool = False) -> str:
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension as ext
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    inc = ext.include_paths() + [sysconfig.get_paths()["include"], "/opt/rocm/include"]
+    cmd = (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+           + [x for i in inc for x in ("-isystem", i)]
+           + [os.path.join(CSRC, "tensor_check.cpp"), "-o", TENSOR_CHECK + ".tmp", "-L" + lib, "-ltorch_python", "-ltorch",
+              "-ltorch_cpu", "-lc10", "-Wl,-rpath," + lib])
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed for tensor_check.cpp:\n{r.stderr}")
+    os.replace(TENSOR_CHECK + ".tmp", TENSOR_CHECK)
+    return TENSOR_CHECK
 
 
 # The ABI's host code (api.hip: argument checks, layouts, ring state,

@@ -13,6 +13,12 @@ import torch
 from .abi import *  # noqa: F401,F403  (status codes, enums, structs, SIGNATURES)
 from .abi import _STATUS_NAMES, load as _load_abi  # noqa: F401
 
+try:  # built beside libconduit.so; without it every check below runs in Python
+    from ._tensor_check import address as _address
+except ImportError:
+    def _address(t, dtype, nbytes, numel):
+        return None
+
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libconduit.so")
 _lib = None
 
@@ -40,6 +46,8 @@ def _check(status):
 
 def _stream(stream):
     if stream is None:
+        if torch.cuda.is_initialized():  # the current stream's handle without a Stream object around it
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return C.c_void_p(torch.cuda.current_stream().cuda_stream)
     if isinstance(stream, torch.cuda.Stream):
         return C.c_void_p(stream.cuda_stream)
@@ -55,9 +63,13 @@ def _ptr(t, dtype=None, name="tensor", nbytes=None, numel=None):
     its type, dtype (one dtype or a tuple of accepted dtypes), that it holds at
     least `nbytes` bytes / `numel` elements, contiguity and device.  Each
     failure raises before anything reaches the library, so a shape or dtype
-    slip never becomes an out-of-bounds device access."""
+    slip never becomes an out-of-bounds device access.  A tensor that passes them
+    all natively (_tensor_check) is done; any other is checked here."""
     if t is None:
         return None
+    p = _address(t, dtype, nbytes, numel)
+    if p is not None:
+        return p
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch tensor")
     if dtype is not None:

@@ -676,7 +676,7 @@ conduit_status conduit_update_ingest(conduit_buffer* b, const int64_t* idx, cons
     // derived episode/step columns first: the update does not read them
     hipError_t e = t->n > 0 ? launch_derive_meta(a, s) : hipSuccess;
     if (e == hipSuccess) {
-        if (n_update > 0 && t->n > 0 && !b->opts.ragged && t->n <= kFusedIngestMaxRows) {
+        if (n_update > 0 && t->n > 0 && t->n <= kFusedIngestMaxRows) {
             e = launch_update_ingest(u, a, s);
         } else {  // the same two operations, one launch each
             if (n_update > 0) e = launch_update(u, s);

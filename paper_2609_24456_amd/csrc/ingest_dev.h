@@ -12,7 +12,6 @@ namespace {
 constexpr int kIngestThreads = 256;  // threads of one ingest (sub-)block
 constexpr int kCopyUnroll = 4;
 constexpr int kActWords = 8;  // action words of a row held in registers
-constexpr int kRaggedUnroll = 8;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -72,7 +71,13 @@ __device__ __forceinline__ bool ragged_span(const IngestArgs& a, int64_t j, int6
     return ok;
 }
 
+// Row j by NT lanes, U vectors of four elements per lane and pass, every load
+// ahead of the stores.  The source starts at any element (4-byte alignment, which
+// is all a 16-byte load needs), the slot at a 16-byte boundary; the last lane in
+// the row takes a remainder of up to three elements.
+template <int NT, int U>
 __device__ inline void copy_ragged(const IngestArgs& a, int64_t j, int tid) {
+    typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));
     int64_t slot = a.head + j;
     if (slot >= a.capacity) slot -= a.capacity;
     int64_t off, len;
@@ -84,30 +89,33 @@ __device__ inline void copy_ragged(const IngestArgs& a, int64_t j, int tid) {
     const bool aux = a.aux && a.src_aux;
     const uint32_t* __restrict__ sa = aux ? reinterpret_cast<const uint32_t*>(a.src_aux) + off : s;
     uint32_t* __restrict__ da = aux ? reinterpret_cast<uint32_t*>(a.aux) + slot * a.max_len : nullptr;
-    // kRaggedUnroll elements per lane per pass, every load (clamped to the last
-    // element) ahead of the stores
-    for (int64_t t0 = tid; t0 < len; t0 += (int64_t)kIngestThreads * kRaggedUnroll) {
-        uint32_t v[kRaggedUnroll], w[kRaggedUnroll];
+    const int64_t whole = len & ~(int64_t)3;
+    for (int64_t q0 = tid; q0 * 4 < whole; q0 += (int64_t)NT * U) {
+        u32x4 v[U], w[U];
 #pragma unroll
-        for (int r = 0; r < kRaggedUnroll; ++r) {
-            const int64_t t = t0 + (int64_t)r * kIngestThreads;
-            const int64_t tc = t < len ? t : len - 1;
-            v[r] = s[tc];
-            w[r] = sa[tc];
+        for (int r = 0; r < U; ++r) {
+            const int64_t t = (q0 + (int64_t)r * NT) * 4;
+            const int64_t tc = t < whole ? t : whole - 4;  // past the end: the last vector again
+            v[r] = *reinterpret_cast<const u32x4u*>(s + tc);
+            if (aux) w[r] = *reinterpret_cast<const u32x4u*>(sa + tc);
         }
 #pragma unroll
-        for (int r = 0; r < kRaggedUnroll; ++r) {
+        for (int r = 0; r < U; ++r) {
             pin(v[r]);
-            pin(w[r]);
+            if (aux) pin(w[r]);
         }
 #pragma unroll
-        for (int r = 0; r < kRaggedUnroll; ++r) {
-            const int64_t t = t0 + (int64_t)r * kIngestThreads;
-            if (t < len) {
-                d[t] = v[r];
-                if (aux) da[t] = w[r];
+        for (int r = 0; r < U; ++r) {
+            const int64_t t = (q0 + (int64_t)r * NT) * 4;
+            if (t < whole) {
+                __builtin_nontemporal_store(v[r], reinterpret_cast<u32x4*>(d + t));
+                if (aux) __builtin_nontemporal_store(w[r], reinterpret_cast<u32x4*>(da + t));
             }
         }
+    }
+    if (tid < (int)(len - whole)) {
+        d[whole + tid] = s[whole + tid];
+        if (aux) da[whole + tid] = sa[whole + tid];
     }
 }
 

@@ -35,7 +35,7 @@ __global__ __launch_bounds__(kIngestThreads) void k_ingest(IngestArgs a, int64_t
     if (b < meta_blocks) {
         ingest_meta(a, b, threadIdx.x);
     } else {
-        if constexpr (RAGGED) copy_ragged(a, b - meta_blocks, threadIdx.x);
+        if constexpr (RAGGED) copy_ragged<kIngestThreads, 4>(a, b - meta_blocks, threadIdx.x);
         else copy_dense<V>(a, b - meta_blocks, threadIdx.x);
     }
 }

@@ -14,9 +14,13 @@
 //   * every other block is four ingest sub-blocks of 256 lanes (ingest_dev.h):
 //     the new rows' columns, leaves and per-wavefront tree deltas, each
 //     wavefront (of a long list, each block) computing the raised running
-//     maximum from the update list itself, and the payload copy.
+//     maximum from the update list itself, and the payload copy; variable-length
+//     rows take a block each instead (256 sequences of up to 4,096 tokens with
+//     256 updates: 9.2 us as two launches, 5.6 as one).
 // The two sets of leaves are disjoint and every tree change is an integer
 // atomic add, so the result equals the two calls made one after the other.
+#include <type_traits>
+
 #include "ingest_dev.h"
 #include "update_dev.h"
 
@@ -25,6 +29,8 @@ namespace conduit {
 namespace {
 
 constexpr int kSubs = kUpdateThreads / kIngestThreads;
+
+struct Ragged {};  // in the place of the copied vector type: variable-length rows
 
 // The largest valid priority of a list, by the whole workgroup.
 __device__ uint32_t list_max(const RaiseList& u, int32_t* scratch) {
@@ -71,6 +77,15 @@ __global__ __launch_bounds__(kUpdateThreads) void k_update_ingest(UpdateArgs u, 
         raise_max(u.state, seen, pmax);
         return;
     }
+    if constexpr (std::is_same<V, Ragged>::value) {
+        // whole workgroups of metadata, then one per sequence
+        const int64_t meta_wgs = (meta_subs + kSubs - 1) / kSubs;
+        const int64_t j = (int64_t)(blockIdx.x - (uint32_t)groups) - meta_wgs;
+        if (j >= 0) {
+            copy_ragged<kUpdateThreads, 1>(a, j, threadIdx.x);
+            return;
+        }
+    }
     const int64_t sub0 = (int64_t)(blockIdx.x - (uint32_t)groups) * kSubs;
     const int64_t sub = sub0 + threadIdx.x / kIngestThreads;
     const int tid = (int)(threadIdx.x % kIngestThreads);
@@ -87,8 +102,8 @@ __global__ __launch_bounds__(kUpdateThreads) void k_update_ingest(UpdateArgs u, 
         // same priorities: raised_max takes max() over both, so the order of
         // the two parts does not matter
         ingest_meta(a, sub, tid, raise);
-    } else if (sub - meta_subs < copy_subs) {
-        copy_dense<V>(a, sub - meta_subs, tid);
+    } else if constexpr (!std::is_same<V, Ragged>::value) {
+        if (sub - meta_subs < copy_subs) copy_dense<V>(a, sub - meta_subs, tid);
     }
 }
 
@@ -107,7 +122,9 @@ hipError_t launch_update_ingest(const UpdateArgs& u, const IngestArgs& a, hipStr
     const int64_t total_vec = a.n * (a.row_bytes / vec);
     const int64_t copy_subs = (total_vec + kIngestThreads * kCopyUnroll - 1) / (kIngestThreads * kCopyUnroll);
     const int32_t groups = update_groups(u.n);
-    const dim3 grid((unsigned)(groups + (meta_subs + copy_subs + kSubs - 1) / kSubs)), block(kUpdateThreads);
+    const int64_t meta_wgs = (meta_subs + kSubs - 1) / kSubs;
+    const dim3 grid((unsigned)(groups + (a.length ? meta_wgs + a.n : (meta_subs + copy_subs + kSubs - 1) / kSubs)));
+    const dim3 block(kUpdateThreads);
     auto go = [&](auto v) {
         typedef decltype(v) V;
         if (groups == 1)
@@ -117,6 +134,10 @@ hipError_t launch_update_ingest(const UpdateArgs& u, const IngestArgs& a, hipStr
         else
             hipLaunchKernelGGL((k_update_ingest<V, 8>), grid, block, 0, s, u, a, meta_subs, copy_subs, groups);
     };
+    if (a.length) {
+        go(Ragged{});
+        return hipGetLastError();
+    }
     switch (vec) {
         case 16: go(u32x4{}); break;
         case 8: go(u32x2{}); break;

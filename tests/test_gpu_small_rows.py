@@ -159,3 +159,62 @@ def test_sample_gather_small_rows(shape, K, kind, B, norm):
         assert_weights_close(host(w2), o_w)
     assert buf.sync_check() == cd.OK, cd.last_error()
     buf.close()
+
+
+# the one-launch update + ingest of variable-length rows against the two calls
+# (which other tests hold against the oracle): evicted slots among the updates, a
+# wrap, rows of 0 to 5 elements and of a whole slot, too long and at bad offsets,
+# short and long update lists, with and without log-probabilities and priorities
+@pytest.mark.parametrize("max_len,n_update,aux,given", [(8, 40, True, False), (8, 2300, False, True),
+                                                        (5000, 300, True, True), (4100, 2048, True, False)])
+def test_update_ingest_ragged_rows(max_len, n_update, aux, given):
+    print(f"ragged update_ingest max_len={max_len} n_update={n_update}", flush=True)
+    rng = np.random.default_rng(max_len + n_update)
+    cap, n = 300, 130
+    bufs = [cd.ReplayBuffer(cap, (max_len,), torch.int32, ragged=True, aux_elem_bytes=4 if aux else 0) for _ in range(2)]
+    for it in range(4):
+        length = rng.integers(0, max_len + 1, n)
+        length[:8] = [0, 1, 2, 3, 4, 5, max_len, max_len]
+        bad = it == 3
+        if bad:
+            length[20] = max_len + 3  # stored truncated
+        offsets = np.concatenate([[0], np.cumsum(length)])
+        total = int(offsets[-1])
+        tok = rng.integers(0, 1 << 30, total).astype(np.int32)
+        rows = dict(offsets=dev(offsets), action=dev(rng.integers(0, 256, (n, 4), dtype=np.uint8)),
+                    reward=dev(rng.standard_normal(n).astype(np.float32)))
+        if aux:
+            rows["aux"] = dev(rng.standard_normal(total).astype(np.float32))
+        if given:
+            rows["prio"] = dev(synth.quantise_priority(rng.lognormal(0, 1, n)))
+        size = min(cap, it * n)
+        idx = dev(rng.integers(0, max(size, 1), n_update))
+        prio = dev(synth.quantise_priority(rng.lognormal(0, 2, n_update)))
+        if size:
+            bufs[0].update_ingest(idx, prio, dev(tok), **rows)
+            bufs[1].update(idx, prio)
+        else:
+            bufs[0].ingest(dev(tok), **rows)
+        bufs[1].ingest(dev(tok), **rows)
+        assert [b.sync_check() for b in bufs] == [cd.ESTATE if bad else cd.OK] * 2
+        for b in bufs:
+            b.clear_error()
+        info = bufs[0].info()
+        cols = [(cd.COL_LENGTH, cap * 4), (cd.COL_ACTION, cap * 4), (cd.COL_REWARD, cap * 4), (cd.COL_LEAVES, cap * 4),
+                (cd.COL_MAX_PRIO, 4)]
+        a, b = ([read_col(x, c, k, np.uint8) for c, k in cols] for x in bufs)
+        lens = a[0].view(np.int32)[:min(cap, (it + 1) * n)]
+        live = np.arange(max_len)[None, :] < lens[:, None]
+        for x, y in zip(a, b):
+            assert np.array_equal(x[:len(lens) * (len(x) // cap) or len(x)], y[:len(lens) * (len(y) // cap) or len(y)])
+        for c in (cd.COL_OBS, cd.COL_AUX) if aux else (cd.COL_OBS,):
+            x, y = (read_col(z, c, cap * max_len * 4, np.int32).reshape(cap, max_len)[:len(lens)] for z in bufs)
+            assert np.array_equal(x[live], y[live])
+        got = read_col(bufs[0], cd.COL_OBS, cap * max_len * 4, np.int32).reshape(cap, max_len)
+        for j in range(n):  # this ingest's rows, as given
+            k = min(int(length[j]), max_len)
+            assert np.array_equal(got[(it * n + j) % cap, :k], tok[offsets[j]:offsets[j] + k])
+        tree_consistent(bufs[0], cap)
+        assert info.size == min(cap, (it + 1) * n)
+    for b in bufs:
+        b.close()

@@ -6,7 +6,8 @@
 // the batch, Sec. 2.2).
 //
 // Two kinds of 512-lane workgroup share the grid:
-//   * gather workgroups (the head of the grid, one per sample): wavefront 0
+//   * gather workgroups (the head of the grid, one per sample, or up to four in
+//     small batches): wavefront 0
 //     runs tree_descend (descend.h) for the sample -- a few KB of tree reads
 //     -- so the frame loads never wait for another workgroup or for the index
 //     to make a round trip through memory; then the two 256-lane halves split
@@ -81,9 +82,22 @@ __device__ void sampler_wg(const SampleArgs& sa, const DivB& dv, int64_t wg) {
     }
 }
 
+// Workgroups per sample: small batches give a sample several, each descending on
+// its own, as long as all of them are resident at once (kResidentWgs) and each
+// half has an item (128 samples of four 84x84 frames 10.2 -> 8.2 us, with 3-step
+// targets and bootstrap stacks 16.0 -> 11.2; 512 samples take one: two would need
+// a second residency round, 34.8 against 31.0 us with the targets).
+constexpr int64_t kResidentWgs = 512;
+
+inline int32_t wgs_per_sample(int64_t batch, int64_t items) {
+    int32_t w = 1;
+    while (w < 4 && batch * (2 * w) <= kResidentWgs && 4 * w <= items) w *= 2;
+    return w;
+}
+
 template <int XF, int PRE, int DEPTH>
 __global__ __launch_bounds__(kWg) void k_sample_gather(SampleArgs sa, GatherArgs a, DivB dv, int32_t bpf,
-                                                       int32_t sampler_wgs) {
+                                                       int32_t sampler_wgs, int32_t per_sample) {
     __shared__ uint16_t lut[(XF == CONDUIT_XF_U8_BF16_NORM) ? 4 * 256 : 1];
     __shared__ int64_t s_slot;
     const int64_t gather_wgs = (int64_t)gridDim.x - sampler_wgs;
@@ -91,7 +105,7 @@ __global__ __launch_bounds__(kWg) void k_sample_gather(SampleArgs sa, GatherArgs
         sampler_wg<kWg, PRE, DEPTH>(sa, dv, (int64_t)blockIdx.x - gather_wgs);
         return;
     }
-    const int64_t b = blockIdx.x;
+    const uint32_t b = blockIdx.x / (uint32_t)per_sample, sub = blockIdx.x - b * (uint32_t)per_sample;
     if (threadIdx.x < kWave) {
         const Descent d = tree_descend<PRE, DEPTH>(sa.tree, sa.uniforms, b, dv);
         if (threadIdx.x == 0) s_slot = d.slot;
@@ -99,11 +113,11 @@ __global__ __launch_bounds__(kWg) void k_sample_gather(SampleArgs sa, GatherArgs
         build_lut(a, lut, kWave, kWg - kWave);
     }
     __syncthreads();
-    // half h of the workgroup takes the row's items as part h of 2 (uniform in
-    // each wavefront: read from the first lane, so that the item's output base
-    // stays a scalar)
+    // each half of the sample's workgroups takes its part of the row's items
+    // (uniform in each wavefront: read from the first lane, so that the item's
+    // output base stays a scalar)
     const int half = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kThreads));
-    gather_row<XF, true>(a, b, half, 2, bpf, s_slot, lut, (int)(threadIdx.x % kThreads));
+    gather_row<XF, true>(a, b, (int)sub * 2 + half, 2 * per_sample, bpf, s_slot, lut, (int)(threadIdx.x % kThreads));
 }
 
 // Rows of few units (vector observations, small frames): one wavefront per
@@ -254,9 +268,10 @@ struct FusedLaunch {
     template <int PRE, int DEPTH>
     hipError_t operator()() const {
         const int64_t sampler_wgs = (sa.batch + kSamplesPerSamplerWg - 1) / kSamplesPerSamplerWg;
-        const dim3 grid((unsigned)(sampler_wgs + sa.batch)), block(kWg);
+        const int32_t w = wgs_per_sample(sa.batch, bpf * ga.stack);
+        const dim3 grid((unsigned)(sampler_wgs + sa.batch * w)), block(kWg);
         hipLaunchKernelGGL((k_sample_gather<XF, PRE, DEPTH>), grid, block, 0, s, sa, ga, dv, (int32_t)bpf,
-                           (int32_t)sampler_wgs);
+                           (int32_t)sampler_wgs, w);
         return hipGetLastError();
     }
 };
@@ -280,12 +295,10 @@ hipError_t launch_xf(const SampleArgs& sa, const GatherArgs& ga, hipStream_t s, 
 // second barrier, with the bootstrap slot known, they convert and store every
 // frame once into the stacks it belongs to.  Sampler workgroups as in
 // k_sample_gather.
-constexpr int kNstepWgsPerSample = 1;  // 512-lane workgroups per sample (2: 34.8 against 31.0 us per DQN batch, n = 3; past one residency round)
-
 template <int XF, int PRE, int DEPTH>
 __global__ __launch_bounds__(kWg) void k_sample_gather_nstep(SampleArgs sa, GatherArgs a, NstepArgs na,
                                                              void* next_out, DivB dv, int32_t bpf,
-                                                             int32_t sampler_wgs) {
+                                                             int32_t sampler_wgs, int32_t per_sample) {
     __shared__ uint16_t lut[(XF == CONDUIT_XF_U8_BF16_NORM) ? 4 * 256 : 1];
     __shared__ int64_t s_slot, s_next;
     const int64_t gather_wgs = (int64_t)gridDim.x - sampler_wgs;
@@ -293,8 +306,8 @@ __global__ __launch_bounds__(kWg) void k_sample_gather_nstep(SampleArgs sa, Gath
         sampler_wg<kWg, PRE, DEPTH>(sa, dv, (int64_t)blockIdx.x - gather_wgs);
         return;
     }
-    const int64_t b = blockIdx.x / kNstepWgsPerSample;
-    const int sub = (int)(blockIdx.x % kNstepWgsPerSample);
+    const uint32_t b = blockIdx.x / (uint32_t)per_sample;
+    const int sub = (int)(blockIdx.x - b * (uint32_t)per_sample);
     WindowLoads win;
     if (threadIdx.x < kWave) {
         const Descent d = tree_descend<PRE, DEPTH>(sa.tree, sa.uniforms, b, dv);
@@ -317,7 +330,7 @@ __global__ __launch_bounds__(kWg) void k_sample_gather_nstep(SampleArgs sa, Gath
     }
     __syncthreads();  // the bootstrap slot is known
     r.jn = r.S > 0 ? s_next : -1;
-    g.run(a, r, part, 2 * kNstepWgsPerSample, bpf, next_out, lut, tid);
+    g.run(a, r, part, 2 * per_sample, bpf, next_out, lut, tid);
 }
 
 template <int XF>
@@ -332,9 +345,11 @@ struct FusedNstepLaunch {
     template <int PRE, int DEPTH>
     hipError_t operator()() const {
         const int64_t sampler_wgs = (sa.batch + kSamplesPerSamplerWg - 1) / kSamplesPerSamplerWg;
-        const dim3 grid((unsigned)(sampler_wgs + sa.batch * kNstepWgsPerSample)), block(kWg);
+        const int64_t frames = ga.stack + (next_out ? (na.n < ga.stack ? na.n : ga.stack) : 0);
+        const int32_t w = wgs_per_sample(sa.batch, bpf * frames);
+        const dim3 grid((unsigned)(sampler_wgs + sa.batch * w)), block(kWg);
         hipLaunchKernelGGL((k_sample_gather_nstep<XF, PRE, DEPTH>), grid, block, 0, s, sa, ga, na, next_out, dv,
-                           (int32_t)bpf, (int32_t)sampler_wgs);
+                           (int32_t)bpf, (int32_t)sampler_wgs, w);
         return hipGetLastError();
     }
 };

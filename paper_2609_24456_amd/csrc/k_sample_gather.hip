@@ -371,17 +371,14 @@ hipError_t launch_nstep_xf(const SampleArgs& sa, const GatherArgs& ga, const Nst
 // length and reward it has just written (gae_packed_row), as
 // conduit_gae_packed would over the packed batch.
 //
-// Widths, measured on [256, 4096] token batches: the pack alone takes 256
-// lanes (7.4 us; 7.8-8.3 us with 512), the pack + GAE 512 lanes (10.3 us
-// against 12.1 us with 256: the row's recursion is 8 steps per lane instead
-// of 16).
-template <bool GAE>
-constexpr int pack_wg() { return GAE ? 512 : kThreads; }
-
-template <int PRE, int DEPTH, bool GAE>
-__global__ __launch_bounds__(pack_wg<GAE>()) void k_sample_pack(SampleArgs sa, PackArgs pa, GaePackedArgs ga,
-                                                                DivB dv, int32_t sampler_wgs) {
-    constexpr int NT = pack_wg<GAE>();
+// Widths: the pack alone takes 256 lanes ([256, 4096]: 7.4 us; 7.8-8.3 us with
+// 512).  Pack + GAE take the row in one pass of at most 2 vectors per lane: 256
+// lanes up to 1,024 elements ([1000, 256] 12.0 us against 13.4 with 512 lanes), 512
+// up to 4,096 ([256, 4096] 9.8 us; 11.6 with 256, 12.0 with 1,024), 1,024 beyond
+// ([200, 8192] 12.1 us against 13.9).
+template <int NT, int PRE, int DEPTH, bool GAE>
+__global__ __launch_bounds__(NT) void k_sample_pack(SampleArgs sa, PackArgs pa, GaePackedArgs ga, DivB dv,
+                                                    int32_t sampler_wgs) {
     __shared__ int64_t s_slot;
     const int64_t pack_wgs = (int64_t)gridDim.x - sampler_wgs;
     if ((int64_t)blockIdx.x >= pack_wgs) {
@@ -395,7 +392,7 @@ __global__ __launch_bounds__(pack_wg<GAE>()) void k_sample_pack(SampleArgs sa, P
     }
     __syncthreads();
     const PackedRow row = pack_row<NT>(pa, b, s_slot);
-    if constexpr (GAE) gae_packed_row<NT, 2>(ga, b, row.L, (double)row.R);
+    if constexpr (GAE) gae_packed_row<NT, NT == kThreads ? 1 : 2>(ga, b, row.L, (double)row.R);
 }
 
 struct PackLaunch {
@@ -404,18 +401,20 @@ struct PackLaunch {
     const GaePackedArgs* ga;  // NULL: no GAE
     DivB dv;
     hipStream_t s;
-    template <bool GAE, int PRE, int DEPTH>
+    template <int NT, bool GAE, int PRE, int DEPTH>
     hipError_t launch() const {
-        constexpr int NT = pack_wg<GAE>();
         const int64_t sampler_wgs = (sa.batch + NT / kWave - 1) / (NT / kWave);
         const dim3 grid((unsigned)(sampler_wgs + sa.batch)), block(NT);
-        hipLaunchKernelGGL((k_sample_pack<PRE, DEPTH, GAE>), grid, block, 0, s, sa, pa, ga ? *ga : GaePackedArgs{},
+        hipLaunchKernelGGL((k_sample_pack<NT, PRE, DEPTH, GAE>), grid, block, 0, s, sa, pa, ga ? *ga : GaePackedArgs{},
                            dv, (int32_t)sampler_wgs);
         return hipGetLastError();
     }
     template <int PRE, int DEPTH>
     hipError_t operator()() const {
-        return ga ? launch<true, PRE, DEPTH>() : launch<false, PRE, DEPTH>();
+        if (!ga) return launch<kThreads, false, PRE, DEPTH>();
+        if (pa.max_len <= 1024) return launch<kThreads, true, PRE, DEPTH>();
+        if (pa.max_len <= 4096) return launch<512, true, PRE, DEPTH>();
+        return launch<1024, true, PRE, DEPTH>();
     }
 };
 

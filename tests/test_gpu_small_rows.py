@@ -220,3 +220,43 @@ def test_update_ingest_ragged_rows(max_len, n_update, aux, given):
         assert info.size == min(cap, (it + 1) * n)
     for b in bufs:
         b.close()
+
+
+# token delivery with advantages at each width it is dispatched on (256, 512 and
+# 1,024 lanes), against the two calls it stands for
+@pytest.mark.parametrize("max_len,B", [(4, 3), (1024, 130), (1028, 70), (4096, 33), (4100, 40)])
+@pytest.mark.parametrize("values", [False, True])
+def test_sample_pack_gae_widths(max_len, B, values):
+    print(f"pack + gae max_len={max_len} B={B} values={values}", flush=True)
+    rng = np.random.default_rng(max_len + B)
+    cap = 150
+    length = rng.integers(0, max_len + 1, cap)
+    length[:3] = [0, 1, max_len]
+    total = int(length.sum())
+    buf = cd.ReplayBuffer(cap, (max_len,), torch.int32, ragged=True, aux_elem_bytes=4)
+    buf.ingest(dev(rng.integers(0, 1 << 30, total).astype(np.int32)), aux=dev(rng.standard_normal(total).astype(np.float32)),
+               offsets=dev(np.concatenate([[0], np.cumsum(length)])), reward=dev(rng.standard_normal(cap).astype(np.float32)),
+               prio=dev(synth.quantise_priority(rng.lognormal(0, 1, cap))))
+    u = dev(synth.uniforms(rng, B))
+    v = dev(rng.standard_normal((B, max_len)).astype(np.float32)) if values else None
+    xf = cd.transform(cd.XF_TOKENS_PAD, pad_id=7)
+    outs = []
+    for fused in (True, False):
+        f = lambda *s: torch.full(s, np.nan, device="cuda")  # noqa: E731
+        o = dict(obs=torch.zeros((B, max_len), dtype=torch.int32, device="cuda"), aux=f(B, max_len), reward=f(B),
+                 mask=torch.zeros((B, max_len), dtype=torch.uint8, device="cuda"),
+                 length=torch.zeros(B, dtype=torch.int32, device="cuda"))
+        adv, ret = f(B, max_len), f(B, max_len)
+        if fused:
+            idx, w = buf.sample_pack_gae(u, xf, 0.99, 0.95, adv, ret, values=v, **o)
+        else:
+            idx, w = buf.sample_gather(u, xf, **o)
+            cd.conduit_gae_packed(o["reward"], o["length"], v, max_len, 0.99, 0.95, adv, ret)
+        assert buf.sync_check() == cd.OK and cd.conduit_sync_check() == cd.OK
+        outs.append((idx, w, adv, ret, *o.values()))
+    for x, y in zip(*outs):
+        if x.dtype == torch.float32:
+            assert_gae_close(host(x), host(y))
+        else:
+            assert torch.equal(x, y)
+    buf.close()

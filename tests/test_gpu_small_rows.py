@@ -7,7 +7,7 @@ import torch
 
 import oracle
 import synth
-from gpu_util import assert_weights_close, dev, host, read_col, tree_consistent
+from gpu_util import assert_gae_close, assert_weights_close, dev, host, read_col, tree_consistent
 from paper_2609_24456_amd import conduit as cd
 
 pytestmark = pytest.mark.gpu

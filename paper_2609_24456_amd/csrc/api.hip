@@ -748,7 +748,8 @@ static void fill_norm(GatherArgs& a, const conduit_transform* xf, int64_t row_by
         return;
     }
     a.plane_units = (int32_t)(row_bytes / 4 / xf->channels);
-    a.by_plane = make_div31((uint32_t)a.plane_units);
+    // a minibatch of columns alone has rows of 0 bytes: no plane to divide by
+    a.by_plane = make_div31(a.plane_units ? (uint32_t)a.plane_units : 1u);
     for (int c = 0; c < 4; ++c) {
         a.mean[c] = c < xf->channels ? xf->mean[c] : 0.0f;
         a.stdv[c] = c < xf->channels ? xf->std[c] : 1.0f;

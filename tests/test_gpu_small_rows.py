@@ -51,6 +51,24 @@ def test_minibatch_flat_rows(planes, units, kind, n, offset):
             assert np.array_equal(host(o)[ok], c[idx[ok]]) and not host(o)[~ok].any()
 
 
+# columns alone: rows of 0 bytes, with and without an output pointer, under every transform
+@pytest.mark.parametrize("kind", [cd.XF_NONE, cd.XF_U8_F32, cd.XF_U8_BF16_NORM])
+@pytest.mark.parametrize("pointer", [False, True])
+def test_minibatch_columns_alone(kind, pointer):
+    print(f"columns alone kind={kind} pointer={pointer}", flush=True)
+    rng = np.random.default_rng(kind)
+    cols = [rng.standard_normal(40).astype(np.float32) for _ in range(2)]
+    perm = rng.permutation(40)[:33]
+    xf = cd.transform(kind, MEAN[:3], STD[:3]) if kind == cd.XF_U8_BF16_NORM else cd.transform(kind)
+    rows = torch.full((16,), 9, dtype=torch.uint8, device="cuda") if pointer else None
+    cols_out = [torch.full((33,), np.nan, device="cuda") for _ in cols]
+    cd.conduit_minibatch_gather(rows, 0, 40, dev(perm), xf, rows, [dev(c) for c in cols], cols_out)
+    assert cd.conduit_sync_check() == cd.OK, cd.last_error()
+    for c, o in zip(cols, cols_out):
+        assert np.array_equal(host(o), c[perm])
+    assert rows is None or (host(rows) == 9).all()
+
+
 # update lists around the split (2,048), with the last pass partial and whole
 # (4 and 8 entries per lane), several passes, repeats throughout, indices out of
 # range, and lists whose slots all fall to one of the 64 workgroups (more than

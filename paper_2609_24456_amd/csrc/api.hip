@@ -742,14 +742,8 @@ static conduit_status check_xform(const conduit_transform* xf, int64_t row_bytes
 }
 
 static void fill_norm(GatherArgs& a, const conduit_transform* xf, int64_t row_bytes) {
-    if (xf->kind != CONDUIT_XF_U8_BF16_NORM) {
-        a.plane_units = 1;
-        a.by_plane = make_div31(1);
-        return;
-    }
-    a.plane_units = (int32_t)(row_bytes / 4 / xf->channels);
-    // a minibatch of columns alone has rows of 0 bytes: no plane to divide by
-    a.by_plane = make_div31(a.plane_units ? (uint32_t)a.plane_units : 1u);
+    if (xf->kind != CONDUIT_XF_U8_BF16_NORM) return;
+    a.planes = make_planes(xf->channels, row_bytes / 4 / xf->channels);
     for (int c = 0; c < 4; ++c) {
         a.mean[c] = c < xf->channels ? xf->mean[c] : 0.0f;
         a.stdv[c] = c < xf->channels ? xf->std[c] : 1.0f;

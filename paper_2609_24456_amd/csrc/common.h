@@ -155,6 +155,27 @@ __host__ __device__ __forceinline__ uint32_t div31(uint32_t n, const Div31& v) {
     return (uint32_t)(((uint64_t)n * v.m) >> v.sh);
 }
 
+// The plane (0 to 3) of 4-byte unit u of a frame of up to four equal planes, by
+// comparison with the last unit of each plane but the last: a frame may have more
+// units than Div31 takes, and a plane beyond the last would be past its table.
+struct Planes {
+    int32_t n;
+    uint32_t last[3];  // UINT32_MAX: no plane after this one
+};
+
+inline Planes make_planes(int32_t n, int64_t units_per_plane) {
+    Planes p{n, {}};
+    for (int32_t k = 0; k < 3; ++k) {
+        const int64_t last = (k + 1) * units_per_plane - 1;
+        p.last[k] = k + 1 < n && last < 0xffffffffll ? (uint32_t)(last < 0 ? 0 : last) : 0xffffffffu;
+    }
+    return p;
+}
+
+__host__ __device__ __forceinline__ uint32_t plane_of(uint32_t u, const Planes& p) {
+    return (u > p.last[0] ? 1u : 0u) + (u > p.last[1] ? 1u : 0u) + (u > p.last[2] ? 1u : 0u);
+}
+
 // ---------------------------------------------------------------------------
 // exact leaf quantiser  L(p) = floor(2^F p^(a/b))
 // ---------------------------------------------------------------------------
@@ -424,8 +445,7 @@ struct GatherArgs {
     const int32_t* step;
     void* out;
     int32_t xform;          // conduit_xform_kind
-    int32_t plane_units;    // U8_BF16_NORM: 4-byte units per plane
-    Div31 by_plane;         // ... and the division by it
+    Planes planes;          // U8_BF16_NORM
     float mean[4];
     float stdv[4];
     // scalar columns taken from the newest slot

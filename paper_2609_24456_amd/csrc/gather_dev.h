@@ -106,8 +106,7 @@ __device__ inline void gather_scalars(const GatherArgs& a, int64_t block) {
 // per-workgroup table of the exact u8 -> bf16 normalisation, 256 entries per
 // plane, built by lanes [first, first + count)
 __device__ __forceinline__ void build_lut(const GatherArgs& a, uint16_t* lut, int first = 0, int count = kThreads) {
-    const int planes = (int)((a.row_bytes >> 2) / a.plane_units);
-    for (int e = (int)threadIdx.x - first; e < planes * 256; e += count) {
+    for (int e = (int)threadIdx.x - first; e < a.planes.n * 256; e += count) {
         const int c = e >> 8;
         const float v = u8_unit_f32((uint32_t)(e & 255));
         const float centred = v - a.mean[c];
@@ -293,7 +292,7 @@ __device__ __forceinline__ void finish(const GatherArgs& a, const Item& t, const
         for (int r = 0; r < kUnroll; ++r) {
             const int64_t u = u0 + (int64_t)r * kThreads;
             const uint32_t uu = (uint32_t)(u < units ? u : units - 1);  // keeps the plane index in range
-            const uint16_t* tb = lut + div31(uu, a.by_plane) * 256;
+            const uint16_t* tb = lut + plane_of(uu, a.planes) * 256;
             const uint32_t x = v[r];
             const uint32_t lo = (uint32_t)tb[x & 255u] | ((uint32_t)tb[(x >> 8) & 255u] << 16);
             const uint32_t hi = (uint32_t)tb[(x >> 16) & 255u] | ((uint32_t)tb[x >> 24] << 16);
@@ -455,7 +454,7 @@ __device__ __forceinline__ typename OutUnit<XF>::T convert_unit(const GatherArgs
         o.z = u8_unit_f32((x >> 16) & 255u);
         o.w = u8_unit_f32(x >> 24);
     } else {  // U8_BF16_NORM
-        const uint16_t* tb = lut + div31(u, a.by_plane) * 256;
+        const uint16_t* tb = lut + plane_of(u, a.planes) * 256;
         o.x = (uint32_t)tb[x & 255u] | ((uint32_t)tb[(x >> 8) & 255u] << 16);
         o.y = (uint32_t)tb[(x >> 16) & 255u] | ((uint32_t)tb[x >> 24] << 16);
     }

@@ -525,7 +525,8 @@ conduit_status conduit_gae_plan(int64_t T, int64_t E, int32_t aligned, int32_t* 
  * App. A, the table mapping Verl's stages): sequence b of length L = lengths[b] receives the
  * scalar last_reward[b] on element L-1, which also ends it; all other rewards
  * are 0.  values: device float [B, Lmax] or NULL (0).  adv, ret: device float
- * [B, Lmax]; positions t >= L are written as 0.  fp64 inside.
+ * [B, Lmax], apart from each other; either may be `values` itself (in place);
+ * positions t >= L are written as 0.  fp64 inside.
  * Lengths outside [0, Lmax] are flagged and clamped.
  * Errors: EINVAL, ESTATE.
  */

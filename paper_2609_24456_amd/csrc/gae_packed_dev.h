@@ -130,12 +130,17 @@ struct LanePowers {
 // ends before the sequence's last element has the same coefficient everywhere,
 // so only the S parts of its maps are scanned (LanePowers): the fp64 arithmetic
 // bounds the kernel as much as the chain of its latencies does.  The next pass's
-// values load before the current one is worked on; padding is not read.
+// values load before the current one is worked on; padding is not read.  Outputs
+// may take the values' place: a wavefront stores only elements it has loaded
+// itself, and the one value it needs of another's span is used before that
+// wavefront stores (or comes through LDS, from the later pass's first wavefront).
 // Against staging each row through LDS, 4,096 elements at a time: [256, 8192] 9.3
 // -> 8.0 us, [244, 16384] 16.0 -> 11.4, rows off 16 bytes [244, 16383] 23.0 ->
 // 11.2, [1024, 1024] 10.2 -> 5.8, [1024, 4096] 14.0 -> 11.8; the fused sample +
 // pack + GAE of [1024, 1024] 21.3 -> 19.2.
-template <int NT, int J>
+// ONE: one pass takes the row (Lmax <= 4 NT J); compiled without the next pass's
+// registers ([1000, 4000] 10.4 -> 9.1 us, [1024, 2000] 8.2 -> 7.2).
+template <int NT, int J, bool ONE>
 __device__ void gae_packed_row(const GaePackedArgs& a, int64_t b, int64_t L, double R) {
     if (!a.value) {  // kernel argument: uniform
         gae_packed_row_novalue<NT>(a, b, L, R);
@@ -145,15 +150,17 @@ __device__ void gae_packed_row(const GaePackedArgs& a, int64_t b, int64_t L, dou
     constexpr int64_t kWaveSpan = 4 * kWave * J;  // elements of a wavefront and pass
     constexpr int64_t kPass = kWaveSpan * kWaves;
     __shared__ double sWP[2][kWaves], sWS[2][kWaves];
+    __shared__ float sV[2][kWaves];  // the wavefronts' first values
     const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), lane = lane_id();
     const int64_t Lmax = a.Lmax;
-    const float* __restrict__ val = a.value + b * Lmax;
+    const float* val = a.value + b * Lmax;  // may be adv or ret
     float* adv = a.adv + b * Lmax;
     float* ret = a.ret + b * Lmax;
     const double gl = a.gamma * a.lambda;
     const int own = (kWave - 1 - lane) * 4;  // the lane's vector in a block
     // the lane's vectors of the pass at `base`, and the value after the
-    // wavefront's span (0 where nothing live lies there)
+    // wavefront's span (0 where nothing live lies there, and for the last
+    // wavefront, whose next value is the later pass's)
     auto load = [&](int64_t base, f32x4 (&v)[J], float& after) {
         const int64_t w0 = base + wv * kWaveSpan;
 #pragma unroll
@@ -170,7 +177,7 @@ __device__ void gae_packed_row(const GaePackedArgs& a, int64_t b, int64_t L, dou
             }
         }
         const int64_t e = w0 + kWaveSpan;
-        after = e < L ? val[e] : 0.0f;
+        after = wv < kWaves - 1 && e < L ? val[e] : 0.0f;
     };
     auto put = [&](int64_t t, const f32x4& x, const f32x4& y) {
         if (t + 3 < Lmax) {
@@ -199,7 +206,7 @@ __device__ void gae_packed_row(const GaePackedArgs& a, int64_t b, int64_t L, dou
     if (base >= 0) load(base, v, after);
     double carry = 0.0;  // A at the start of the later pass
     for (int par = 0; base >= 0; base -= kPass, par ^= 1) {
-        if (base > 0) load(base - kPass, vn, after_n);
+        if (!ONE && base > 0) load(base - kPass, vn, after_n);
         const int64_t w0 = base + wv * kWaveSpan;
         double end[J];            // V after the lane's vector
         double eP[J], eS[J];      // the block's later lanes
@@ -265,9 +272,10 @@ __device__ void gae_packed_row(const GaePackedArgs& a, int64_t b, int64_t L, dou
             wS = tS + tP * wS;
             wP = tP * wP;
         }
-        if (lane == 0) {
+        if (lane == kWave - 1) {  // holds the span's first vector
             sWP[par][wv] = wP;
             sWS[par][wv] = wS;
+            if (!ONE) sV[par][wv] = v[0][0];
         }
         lds_barrier();  // the pass before used the other half
         double lP = 1.0, lS = 0.0;  // the later wavefronts
@@ -311,10 +319,11 @@ __device__ void gae_packed_row(const GaePackedArgs& a, int64_t b, int64_t L, dou
             }
             put(t, oa, orr);
         }
+        if constexpr (ONE) break;
         carry = tP * carry + tS;
 #pragma unroll
         for (int j = 0; j < J; ++j) v[j] = vn[j];
-        after = after_n;
+        after = wv == kWaves - 1 ? sV[par][0] : after_n;
     }
 }
 

@@ -1136,7 +1136,7 @@ __global__ __launch_bounds__(kSegThreads) void k_gae_tile(GaeArgs a) {
     replay<TRUNC, L, V4>(a, ch, A, gl, t0, e0, active);
 }
 
-template <int NT, int J>
+template <int NT, int J, bool ONE>
 __global__ __launch_bounds__(NT) void k_gae_packed(GaePackedArgs a) {
     const int64_t b = blockIdx.x;
     int64_t L = a.length[b];
@@ -1144,7 +1144,7 @@ __global__ __launch_bounds__(NT) void k_gae_packed(GaePackedArgs a) {
         if (threadIdx.x == 0) flag_error(a.err, ERR_SEQ_LENGTH);
         L = L < 0 ? 0 : a.Lmax;
     }
-    gae_packed_row<NT, J>(a, b, L, (double)a.last_reward[b]);
+    gae_packed_row<NT, J, ONE>(a, b, L, (double)a.last_reward[b]);
 }
 
 __global__ void k_fill_u32(uint32_t* p, uint32_t v, int64_t n) {
@@ -1378,11 +1378,11 @@ hipError_t launch_gae_packed(const GaePackedArgs& a, hipStream_t s) {
     // the fewest lanes that take a row in one pass with at most 4 vectors each;
     // more lanes only wait for each other ([1024, 1024]: 256 lanes 5.8 us, 512
     // 8.9, 1,024 15.8), more vectors than 2 x 1,024 lanes spill
-    if (a.Lmax <= 1024) hipLaunchKernelGGL((k_gae_packed<256, 1>), grid, dim3(256), 0, s, a);
-    else if (a.Lmax <= 2048) hipLaunchKernelGGL((k_gae_packed<512, 1>), grid, dim3(512), 0, s, a);
-    else if (a.Lmax <= 4096) hipLaunchKernelGGL((k_gae_packed<512, 2>), grid, dim3(512), 0, s, a);
-    else if (a.Lmax <= 8192) hipLaunchKernelGGL((k_gae_packed<512, 4>), grid, dim3(512), 0, s, a);
-    else hipLaunchKernelGGL((k_gae_packed<1024, 2>), grid, dim3(1024), 0, s, a);
+    if (a.Lmax <= 1024) hipLaunchKernelGGL((k_gae_packed<256, 1, true>), grid, dim3(256), 0, s, a);
+    else if (a.Lmax <= 2048) hipLaunchKernelGGL((k_gae_packed<512, 1, true>), grid, dim3(512), 0, s, a);
+    else if (a.Lmax <= 4096) hipLaunchKernelGGL((k_gae_packed<512, 2, true>), grid, dim3(512), 0, s, a);
+    else if (a.Lmax <= 8192) hipLaunchKernelGGL((k_gae_packed<512, 4, true>), grid, dim3(512), 0, s, a);
+    else hipLaunchKernelGGL((k_gae_packed<1024, 2, false>), grid, dim3(1024), 0, s, a);
     return hipGetLastError();
 }
 

@@ -392,7 +392,7 @@ __global__ __launch_bounds__(NT) void k_sample_pack(SampleArgs sa, PackArgs pa, 
     }
     __syncthreads();
     const PackedRow row = pack_row<NT>(pa, b, s_slot);
-    if constexpr (GAE) gae_packed_row<NT, NT == kThreads ? 1 : 2>(ga, b, row.L, (double)row.R);
+    if constexpr (GAE) gae_packed_row<NT, NT == kThreads ? 1 : 2, NT != 1024>(ga, b, row.L, (double)row.R);
 }
 
 struct PackLaunch {

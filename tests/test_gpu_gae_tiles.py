@@ -71,3 +71,20 @@ def test_gae_packed_widths(Lmax, gamma, lam):
     assert_gae_close(host(adv), oa)
     assert_gae_close(host(ret), orr)
     assert not host(adv)[pad].any() and not host(ret)[pad].any()
+
+
+# advantages or returns in the values' place, one pass a row and several
+@pytest.mark.parametrize("Lmax", [700, 4096, 8192, 8193, 16384, 40001])
+@pytest.mark.parametrize("place", ["adv", "ret"])
+def test_gae_packed_in_place(Lmax, place):
+    print(f"packed in place Lmax={Lmax} {place}", flush=True)
+    rng = np.random.default_rng(Lmax)
+    length = np.concatenate([rng.integers(0, Lmax + 1, 300), [0, 1, Lmax - 1, Lmax]]).astype(np.int32)
+    B = len(length)
+    R, v = dev(rng.standard_normal(B).astype(np.float32)), dev(rng.standard_normal((B, Lmax)).astype(np.float32))
+    adv, ret, other = (torch.empty((B, Lmax), device="cuda") for _ in range(3))
+    cd.conduit_gae_packed(R, dev(length), v, Lmax, 0.99, 0.95, adv, ret)
+    outs = (v, other) if place == "adv" else (other, v)
+    cd.conduit_gae_packed(R, dev(length), v, Lmax, 0.99, 0.95, *outs)
+    assert cd.conduit_sync_check() == cd.OK, cd.last_error()
+    assert torch.equal(outs[0], adv) and torch.equal(outs[1], ret)

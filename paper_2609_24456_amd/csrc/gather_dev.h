@@ -542,7 +542,7 @@ __device__ __forceinline__ void union_issue(const GatherArgs& a, const UnionItem
 #pragma unroll
     for (int r = 0; r < kUnroll; ++r) {
         const int64_t u = u0 + (int64_t)r * kThreads;
-        v[r] = __builtin_nontemporal_load(src + (u < units ? u : units - 1));  // (512 samples, n = 3: 31.9 -> 30.5 us)
+        v[r] = src[u < units ? u : units - 1];
     }
     if (a.stack > 1) {  // kernel argument: uniform
         sj = a.step[t.src];

@@ -378,18 +378,17 @@ constexpr int64_t kFusedMaxItemsPerRow = 8;
 constexpr int64_t kFusedNstepMaxItemsPerRow = 16;
 
 // The work items of row b (the slot i, or out of range for a zero row) that
-// 256-lane group `part` of the row's `wgs` owns (tid: the lane in the group),
-// two per group when the row has more than two, double-buffered: the next
-// item's loads are issued before the current item's stores.  The row's first
-// group also writes its scalar columns, after the frames.
+// 256-lane group `part` of the row owns (tid: the lane in the group), `per_group`
+// of them (host-computed: a 64-bit division here costs 0.4 us), double-buffered:
+// the next item's loads are issued before the current item's stores.  The row's
+// first group also writes its scalar columns, after the frames.
 template <int XF, bool NT_LOADS = false>
-__device__ __forceinline__ void gather_row(const GatherArgs& a, int64_t b, int part, int64_t wgs, int32_t bpf,
+__device__ __forceinline__ void gather_row(const GatherArgs& a, int64_t b, int part, int32_t per_group, int32_t bpf,
                                            int64_t i, const uint16_t* lut, int tid) {
     const bool owner = part == 0;
     const int64_t per_row = (int64_t)bpf * a.stack;
-    const int64_t per_wg = (per_row + wgs - 1) / wgs;
-    const int64_t it0 = b * per_row + part * per_wg;
-    int64_t it_end = it0 + per_wg;
+    const int64_t it0 = b * per_row + (int64_t)part * per_group;
+    int64_t it_end = it0 + per_group;
     if (it_end > (b + 1) * per_row) it_end = (b + 1) * per_row;
     if (it0 >= it_end) {
         if (owner) row_scalars_store(a, b, i, row_scalars_load(a, i, tid), tid);

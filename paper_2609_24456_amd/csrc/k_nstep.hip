@@ -39,7 +39,8 @@ __global__ __launch_bounds__(kNstepThreads) void k_nstep(NstepArgs a) {
 // state (a zero row where there is none), as the fused sampler + gather does
 // after its descent.
 template <int XF>
-__global__ __launch_bounds__(kThreads) void k_nstep_gather(NstepArgs na, GatherArgs a, int32_t bpf, int32_t wgs) {
+__global__ __launch_bounds__(kThreads) void k_nstep_gather(NstepArgs na, GatherArgs a, int32_t bpf, int32_t wgs,
+                                                           int32_t per_group) {
     __shared__ uint16_t lut[(XF == CONDUIT_XF_U8_BF16_NORM) ? 4 * 256 : 1];
     __shared__ int64_t s_slot;
     const int64_t b = (int64_t)blockIdx.x / wgs;
@@ -51,14 +52,14 @@ __global__ __launch_bounds__(kThreads) void k_nstep_gather(NstepArgs na, GatherA
         build_lut(a, lut, kWave, kThreads - kWave);
     }
     __syncthreads();
-    gather_row<XF>(a, b, part, wgs, bpf, s_slot, lut, threadIdx.x);
+    gather_row<XF>(a, b, part, per_group, bpf, s_slot, lut, threadIdx.x);
 }
 
 template <int XF>
 hipError_t launch_nstep_gather_xf(const NstepArgs& na, const GatherArgs& ga, int64_t bpf, int64_t wgs,
                                   hipStream_t s) {
     hipLaunchKernelGGL((k_nstep_gather<XF>), dim3((unsigned)(na.batch * wgs)), dim3(kThreads), 0, s, na, ga,
-                       (int32_t)bpf, (int32_t)wgs);
+                       (int32_t)bpf, (int32_t)wgs, (int32_t)((bpf * ga.stack + wgs - 1) / wgs));
     return hipGetLastError();
 }
 

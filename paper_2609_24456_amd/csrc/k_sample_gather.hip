@@ -82,30 +82,40 @@ __device__ void sampler_wg(const SampleArgs& sa, const DivB& dv, int64_t wg) {
     }
 }
 
-// Workgroups per sample: small batches give a sample several, each descending on
-// its own, as long as all of them are resident at once (kResidentWgs) and each
-// half has an item (128 samples of four 84x84 frames 10.2 -> 8.2 us, with 3-step
-// targets and bootstrap stacks 16.0 -> 11.2; 512 samples take one: two would need
-// a second residency round, 34.8 against 31.0 us with the targets).
-constexpr int64_t kResidentWgs = 512;
-
-inline int32_t wgs_per_sample(int64_t batch, int64_t items) {
-    int32_t w = 1;
-    while (w < 4 && batch * (2 * w) <= kResidentWgs && 4 * w <= items) w *= 2;
-    return w;
+// log2 of the workgroups per sample (1, 2 or 4), each descending on its own: a
+// small batch shares its samples out while that leaves at most a workgroup per
+// compute unit and every half an item (128 samples of four 84x84 frames to fp32
+// 15.0 -> 13.9 us a step, with 3-step targets and bootstrap stacks 20.5 -> 16.7; 64
+// of three 116x116 planes to bf16 14.0 -> 12.6).  Two workgroups a unit pay only
+// for samples of many items (256 samples with the targets 24.2 -> 22.4; of four
+// plain frames 14.4 -> 15.9), and with the bf16 table, which each workgroup
+// builds, sharing stops at half a workgroup a unit (128 samples of four frames
+// 12.8 -> 13.1).  Unshared samples have kernels of their own (SHARED false): the
+// shared form's scalars cost 0.4 us (delivery of 100 samples with 1-step targets
+// 8.7 us against 8.3).
+inline int32_t log2_wgs_per_sample(int64_t batch, int64_t items, bool norm) {
+    const int64_t cus = device_cus();
+    int32_t l = 0;
+    while (l < 2) {
+        const int64_t wgs = batch << (l + 1);
+        const bool few = wgs <= (norm ? cus / 2 : cus) && (4 << l) <= items;
+        const bool long_rows = wgs <= 2 * cus && (7 << l) <= items;
+        if (!few && !long_rows) break;
+        ++l;
+    }
+    return l;
 }
 
-template <int XF, int PRE, int DEPTH>
+template <int XF, int PRE, int DEPTH, bool SHARED>
 __global__ __launch_bounds__(kWg) void k_sample_gather(SampleArgs sa, GatherArgs a, DivB dv, int32_t bpf,
-                                                       int32_t sampler_wgs, int32_t per_sample) {
+                                                       int32_t gather_wgs, int32_t log2_wgs, int32_t per_group) {
     __shared__ uint16_t lut[(XF == CONDUIT_XF_U8_BF16_NORM) ? 4 * 256 : 1];
     __shared__ int64_t s_slot;
-    const int64_t gather_wgs = (int64_t)gridDim.x - sampler_wgs;
-    if ((int64_t)blockIdx.x >= gather_wgs) {
+    if (blockIdx.x >= (uint32_t)gather_wgs) {
         sampler_wg<kWg, PRE, DEPTH>(sa, dv, (int64_t)blockIdx.x - gather_wgs);
         return;
     }
-    const uint32_t b = blockIdx.x / (uint32_t)per_sample, sub = blockIdx.x - b * (uint32_t)per_sample;
+    const uint32_t b = SHARED ? blockIdx.x >> log2_wgs : blockIdx.x, sub = SHARED ? blockIdx.x - (b << log2_wgs) : 0u;
     if (threadIdx.x < kWave) {
         const Descent d = tree_descend<PRE, DEPTH>(sa.tree, sa.uniforms, b, dv);
         if (threadIdx.x == 0) s_slot = d.slot;
@@ -117,7 +127,7 @@ __global__ __launch_bounds__(kWg) void k_sample_gather(SampleArgs sa, GatherArgs
     // (uniform in each wavefront: read from the first lane, so that the item's
     // output base stays a scalar)
     const int half = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kThreads));
-    gather_row<XF, true>(a, b, (int)sub * 2 + half, 2 * per_sample, bpf, s_slot, lut, (int)(threadIdx.x % kThreads));
+    gather_row<XF, true>(a, b, (int)sub * 2 + half, per_group, bpf, s_slot, lut, (int)(threadIdx.x % kThreads));
 }
 
 // Rows of few units (vector observations, small frames): one wavefront per
@@ -268,10 +278,16 @@ struct FusedLaunch {
     template <int PRE, int DEPTH>
     hipError_t operator()() const {
         const int64_t sampler_wgs = (sa.batch + kSamplesPerSamplerWg - 1) / kSamplesPerSamplerWg;
-        const int32_t w = wgs_per_sample(sa.batch, bpf * ga.stack);
-        const dim3 grid((unsigned)(sampler_wgs + sa.batch * w)), block(kWg);
-        hipLaunchKernelGGL((k_sample_gather<XF, PRE, DEPTH>), grid, block, 0, s, sa, ga, dv, (int32_t)bpf,
-                           (int32_t)sampler_wgs, w);
+        const int32_t l = log2_wgs_per_sample(sa.batch, bpf * ga.stack, XF == CONDUIT_XF_U8_BF16_NORM);
+        const dim3 grid((unsigned)(sampler_wgs + (sa.batch << l))), block(kWg);
+        const int64_t groups = 2ll << l;
+        const int32_t per_group = (int32_t)((bpf * ga.stack + groups - 1) / groups);
+        if (l)
+            hipLaunchKernelGGL((k_sample_gather<XF, PRE, DEPTH, true>), grid, block, 0, s, sa, ga, dv, (int32_t)bpf,
+                               (int32_t)(sa.batch << l), l, per_group);
+        else
+            hipLaunchKernelGGL((k_sample_gather<XF, PRE, DEPTH, false>), grid, block, 0, s, sa, ga, dv, (int32_t)bpf,
+                               (int32_t)sa.batch, 0, per_group);
         return hipGetLastError();
     }
 };
@@ -295,19 +311,18 @@ hipError_t launch_xf(const SampleArgs& sa, const GatherArgs& ga, hipStream_t s, 
 // second barrier, with the bootstrap slot known, they convert and store every
 // frame once into the stacks it belongs to.  Sampler workgroups as in
 // k_sample_gather.
-template <int XF, int PRE, int DEPTH>
+template <int XF, int PRE, int DEPTH, bool SHARED>
 __global__ __launch_bounds__(kWg) void k_sample_gather_nstep(SampleArgs sa, GatherArgs a, NstepArgs na,
                                                              void* next_out, DivB dv, int32_t bpf,
-                                                             int32_t sampler_wgs, int32_t per_sample) {
+                                                             int32_t gather_wgs, int32_t log2_wgs) {
     __shared__ uint16_t lut[(XF == CONDUIT_XF_U8_BF16_NORM) ? 4 * 256 : 1];
     __shared__ int64_t s_slot, s_next;
-    const int64_t gather_wgs = (int64_t)gridDim.x - sampler_wgs;
-    if ((int64_t)blockIdx.x >= gather_wgs) {
+    if (blockIdx.x >= (uint32_t)gather_wgs) {
         sampler_wg<kWg, PRE, DEPTH>(sa, dv, (int64_t)blockIdx.x - gather_wgs);
         return;
     }
-    const uint32_t b = blockIdx.x / (uint32_t)per_sample;
-    const int sub = (int)(blockIdx.x - b * (uint32_t)per_sample);
+    const uint32_t b = SHARED ? blockIdx.x >> log2_wgs : blockIdx.x;
+    const int sub = SHARED ? (int)(blockIdx.x - (b << log2_wgs)) : 0;
     WindowLoads win;
     if (threadIdx.x < kWave) {
         const Descent d = tree_descend<PRE, DEPTH>(sa.tree, sa.uniforms, b, dv);
@@ -330,7 +345,7 @@ __global__ __launch_bounds__(kWg) void k_sample_gather_nstep(SampleArgs sa, Gath
     }
     __syncthreads();  // the bootstrap slot is known
     r.jn = r.S > 0 ? s_next : -1;
-    g.run(a, r, part, 2 * per_sample, bpf, next_out, lut, tid);
+    g.run(a, r, part, SHARED ? 2 << log2_wgs : 2, bpf, next_out, lut, tid);
 }
 
 template <int XF>
@@ -346,10 +361,14 @@ struct FusedNstepLaunch {
     hipError_t operator()() const {
         const int64_t sampler_wgs = (sa.batch + kSamplesPerSamplerWg - 1) / kSamplesPerSamplerWg;
         const int64_t frames = ga.stack + (next_out ? (na.n < ga.stack ? na.n : ga.stack) : 0);
-        const int32_t w = wgs_per_sample(sa.batch, bpf * frames);
-        const dim3 grid((unsigned)(sampler_wgs + sa.batch * w)), block(kWg);
-        hipLaunchKernelGGL((k_sample_gather_nstep<XF, PRE, DEPTH>), grid, block, 0, s, sa, ga, na, next_out, dv,
-                           (int32_t)bpf, (int32_t)sampler_wgs, w);
+        const int32_t l = log2_wgs_per_sample(sa.batch, bpf * frames, XF == CONDUIT_XF_U8_BF16_NORM);
+        const dim3 grid((unsigned)(sampler_wgs + (sa.batch << l))), block(kWg);
+        if (l)
+            hipLaunchKernelGGL((k_sample_gather_nstep<XF, PRE, DEPTH, true>), grid, block, 0, s, sa, ga, na, next_out, dv,
+                               (int32_t)bpf, (int32_t)(sa.batch << l), l);
+        else
+            hipLaunchKernelGGL((k_sample_gather_nstep<XF, PRE, DEPTH, false>), grid, block, 0, s, sa, ga, na, next_out, dv,
+                               (int32_t)bpf, (int32_t)sa.batch, 0);
         return hipGetLastError();
     }
 };

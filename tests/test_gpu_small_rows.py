@@ -124,8 +124,10 @@ def test_long_update_lists(n, skew, m):
     ((1, 1028), 1, cd.XF_NONE, 1025, 0), ((1, 48), 3, cd.XF_NONE, 2048, 1), ((1, 256), 4, cd.XF_U8_F32, 2049, 0),
     ((3, 80), 4, cd.XF_U8_BF16_NORM, 300, 1), ((2, 128), 4, cd.XF_U8_BF16_NORM, 2503, 1),
     ((1, 4096), 1, cd.XF_NONE, 1024, 1), ((1, 4112), 1, cd.XF_NONE, 1100, 0),
-    # larger rows of small batches: two and four workgroups per sample, and the last batch of two
-    ((1, 7056), 4, cd.XF_U8_F32, 60, 0), ((1, 10000), 4, cd.XF_U8_BF16_NORM, 40, 1), ((1, 7056), 4, cd.XF_NONE, 256, 0)])
+    # larger rows of small batches: one, two and four workgroups per sample, around the last batch of each
+    ((1, 7056), 4, cd.XF_U8_F32, 60, 0), ((1, 10000), 4, cd.XF_U8_BF16_NORM, 40, 1), ((1, 7056), 4, cd.XF_NONE, 256, 0),
+    ((1, 10000), 4, cd.XF_U8_F32, 64, 0), ((1, 10000), 4, cd.XF_U8_F32, 65, 1), ((1, 7056), 4, cd.XF_U8_F32, 128, 0),
+    ((1, 7056), 4, cd.XF_U8_F32, 129, 0), ((1, 7056), 4, cd.XF_U8_BF16_NORM, 64, 0), ((3, 3920), 1, cd.XF_U8_BF16_NORM, 33, 0)])
 def test_sample_gather_small_rows(shape, K, kind, B, norm):
     print(f"small rows shape={shape} K={K} kind={kind} B={B} norm={norm}", flush=True)
     rng = np.random.default_rng(B + K)

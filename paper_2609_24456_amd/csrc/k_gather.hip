@@ -37,11 +37,17 @@ constexpr int64_t kPipeMaxOutBytes = 128ll << 20;
 //   * every frame of up to kFlatMaxUnits units: an item of 1,792 units would
 //     leave most of its lanes idle (24,576 rows of 48 floats, 12 units each:
 //     42.2 us as items, 6.3 us flat; 4,096 40x40 frames to fp32: 10.7 and 7.4);
-//   * single frames of any size, unless normalised to bf16: its non-temporal
-//     contiguous stores beat the persistent kernel's write-through ones and its
-//     even split beats items with a remainder (4,096 84x84 frames to fp32 35 ->
-//     30 us, 88x88 50 -> 32 us; 65,536 rows of 4 KB 114 -> 98 us; 16,384 images
-//     of 3x84x84 to fp32 322 -> 310 us);
+//   * single frames of any size, unless normalised to bf16: its even split beats
+//     items with a remainder, and large outputs leave faster (88x88 50 -> 32 us;
+//     65,536 rows of 4 KB 114 -> 98 us; 16,384 images of 3x84x84 to fp32 322 -> 310
+//     us), except
+//       - frames to fp32 that fill their items and come from HBM (a source beyond
+//         kFlatMaxSource) into up to kPipeMaxOutBytes: the persistent kernel has
+//         more loads in flight (566 84x84 frames of 60,941 5.8 us, 7.1 flat; 2,267
+//         14.9, 18.3; of 2,264 and 9,068 in the last-level cache 5.6, 4.6 and 13.1,
+//         13.6);
+//       - such frames of a sampled batch, whose rows are in address order (a
+//         step of 302 4x120x120 25.6 us, 27.1 flat; of 820 3x224x224 107.8, 115.9);
 //   * single frames of up to kFlatMaxNormUnits units normalised to bf16 (4,096
 //     64x64 frames 15.3 -> 11.8 us); larger ones spend more on finding each
 //     unit's row than they save (1,024 images of 3x224x224: 83 us as items, 98
@@ -51,6 +57,7 @@ constexpr int64_t kPipeMaxOutBytes = 128ll << 20;
 // 12.9 flat).
 constexpr int64_t kFlatMaxUnits = 512;
 constexpr int64_t kFlatMaxNormUnits = 1024;
+constexpr int64_t kFlatMaxSource = 256ll << 20;
 constexpr int kFlatUnroll = 4;         // its most units per lane
 constexpr int64_t kFlatWgsPerCu = 4;   // workgroups per compute unit before a lane takes more units
 constexpr int64_t kFlatLoopWgs = 16;   // bf16: workgroups per compute unit, each looping with its table
@@ -252,7 +259,10 @@ hipError_t launch_gather_xf(const GatherArgs& a, hipStream_t s, int64_t tail_blo
     const int64_t out_bytes = a.n * a.stack * a.row_bytes *
                               (XF == CONDUIT_XF_U8_F32 ? 4 : XF == CONDUIT_XF_U8_BF16_NORM ? 2 : 1);
     const bool norm = XF == CONDUIT_XF_U8_BF16_NORM;
-    const bool flat = units <= kFlatMaxUnits || (a.stack == 1 && (!norm || units <= kFlatMaxNormUnits));
+    // frames to fp32 that fill at least 3/4 of their items
+    const bool full = XF == CONDUIT_XF_U8_F32 && units * 4 >= bpf * kUnitsPerBlock * 3;
+    const bool items = full && (a.weights.w || (a.limit * a.row_bytes > kFlatMaxSource && out_bytes <= kPipeMaxOutBytes));
+    const bool flat = units <= kFlatMaxUnits || (a.stack == 1 && !items && (!norm || units <= kFlatMaxNormUnits));
     const int64_t total = a.n * a.stack * units;
     if (n_items > 0 && flat && total < (1ll << 31) - kThreads * kFlatUnroll) {
         // the most units per lane that still gives every compute unit

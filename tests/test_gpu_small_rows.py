@@ -51,6 +51,24 @@ def test_minibatch_flat_rows(planes, units, kind, n, offset):
             assert np.array_equal(host(o)[ok], c[idx[ok]]) and not host(o)[~ok].any()
 
 
+# frames to fp32 out of sources around the size from which they take the item
+# kernels (256 MiB), filling their items (1,764 of 1,792 units) and not (1,300)
+@pytest.mark.parametrize("units,n", [(1764, 33), (1764, 1500), (1300, 70)])
+@pytest.mark.parametrize("beyond", [False, True])
+def test_minibatch_source_sizes(units, n, beyond):
+    print(f"source sizes units={units} n={n} beyond={beyond}", flush=True)
+    n_src = (256 << 20) // (units * 4) + (1 if beyond else 0)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(units + n)
+    src = torch.randint(-2 ** 31, 2 ** 31, (n_src, units), generator=g, device="cuda", dtype=torch.int32).view(torch.uint8)
+    perm = torch.randint(0, n_src, (n,), generator=g, device="cuda")
+    perm[0], perm[-1] = n_src - 1, 0
+    out = torch.full((n, units * 4), 9.0, device="cuda")
+    cd.conduit_minibatch_gather(src, units * 4, n_src, perm, cd.transform(cd.XF_U8_F32), out)
+    assert cd.conduit_sync_check() == cd.OK, cd.last_error()
+    assert np.array_equal(host(out), host(src[perm]).astype(np.float32) / np.float32(255))
+
+
 # columns alone: rows of 0 bytes, with and without an output pointer, under every transform
 @pytest.mark.parametrize("kind", [cd.XF_NONE, cd.XF_U8_F32, cd.XF_U8_BF16_NORM])
 @pytest.mark.parametrize("pointer", [False, True])
@@ -127,7 +145,9 @@ def test_long_update_lists(n, skew, m):
     # larger rows of small batches: one, two and four workgroups per sample, around the last batch of each
     ((1, 7056), 4, cd.XF_U8_F32, 60, 0), ((1, 10000), 4, cd.XF_U8_BF16_NORM, 40, 1), ((1, 7056), 4, cd.XF_NONE, 256, 0),
     ((1, 10000), 4, cd.XF_U8_F32, 64, 0), ((1, 10000), 4, cd.XF_U8_F32, 65, 1), ((1, 7056), 4, cd.XF_U8_F32, 128, 0),
-    ((1, 7056), 4, cd.XF_U8_F32, 129, 0), ((1, 7056), 4, cd.XF_U8_BF16_NORM, 64, 0), ((3, 3920), 1, cd.XF_U8_BF16_NORM, 33, 0)])
+    ((1, 7056), 4, cd.XF_U8_F32, 129, 0), ((1, 7056), 4, cd.XF_U8_BF16_NORM, 64, 0), ((3, 3920), 1, cd.XF_U8_BF16_NORM, 33, 0),
+    # single frames that fill their items, of a batch beyond the one-launch kernels
+    ((1, 7056), 1, cd.XF_U8_F32, 1100, 1), ((3, 20000), 1, cd.XF_U8_F32, 40, 0)])
 def test_sample_gather_small_rows(shape, K, kind, B, norm):
     print(f"small rows shape={shape} K={K} kind={kind} B={B} norm={norm}", flush=True)
     rng = np.random.default_rng(B + K)

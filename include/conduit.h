@@ -251,9 +251,11 @@ conduit_status conduit_update_priorities(conduit_buffer* buf, const int64_t* idx
  * exactly conduit_update_priorities(buf, idx, prio, n_update) followed by
  * conduit_ingest(buf, t), with the same arguments, effects and errors; either
  * part may be empty (n_update = 0 or t->n = 0).  With both parts and at most
- * 4,096 new rows it takes one launch: one workgroup (several for 2,048 updates
- * and more) applies the updates, while the rest of the grid stores the rows,
- * their columns and their leaves (the update's latency hides behind the copy).  Otherwise the two operations are launched one after the other.
+ * 4,096 new rows (1,024 of variable length) it takes one launch: one workgroup
+ * (several for 2,048 updates and more) applies the updates, while the rest of
+ * the grid stores the rows, their columns and their leaves (the update's latency
+ * hides behind the copy).  Otherwise the two operations are launched one after
+ * the other.
  */
 conduit_status conduit_update_ingest(conduit_buffer* buf, const int64_t* idx, const uint32_t* prio, int64_t n_update,
                                      const conduit_transitions* t, void* stream);

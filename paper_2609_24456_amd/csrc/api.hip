@@ -649,9 +649,13 @@ conduit_status conduit_update_priorities(conduit_buffer* b, const int64_t* idx, 
     return CONDUIT_OK;
 }
 
-// ingests of at most this many rows take the fused launch (its tree pass runs
-// in one workgroup)
+// Ingests of at most this many rows take the fused launch.  Variable-length rows
+// have a workgroup of 1,024 lanes each there, two resident per compute unit, and
+// 256 lanes in the ingest's own launch: 1,024 rows of up to 64 elements take 6.3 us
+// as one launch and 7.9 as two, 2,048 10.0 and 8.2, 4,096 17.4 and 8.4 (of up to
+// 1,024 elements: 6.8 and 8.6, 10.5 and 9.4, 19.2 and 11.8).
 constexpr int64_t kFusedIngestMaxRows = 4096;
+constexpr int64_t kFusedRaggedMaxRows = 1024;
 
 conduit_status conduit_update_ingest(conduit_buffer* b, const int64_t* idx, const uint32_t* prio, int64_t n_update,
                                      const conduit_transitions* t, void* stream) {
@@ -676,7 +680,7 @@ conduit_status conduit_update_ingest(conduit_buffer* b, const int64_t* idx, cons
     // derived episode/step columns first: the update does not read them
     hipError_t e = t->n > 0 ? launch_derive_meta(a, s) : hipSuccess;
     if (e == hipSuccess) {
-        if (n_update > 0 && t->n > 0 && t->n <= kFusedIngestMaxRows) {
+        if (n_update > 0 && t->n > 0 && t->n <= (b->opts.ragged ? kFusedRaggedMaxRows : kFusedIngestMaxRows)) {
             e = launch_update_ingest(u, a, s);
         } else {  // the same two operations, one launch each
             if (n_update > 0) e = launch_update(u, s);

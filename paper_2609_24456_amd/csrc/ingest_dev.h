@@ -73,8 +73,8 @@ __device__ __forceinline__ bool ragged_span(const IngestArgs& a, int64_t j, int6
 
 // Row j by NT lanes, U vectors of four elements per lane and pass, every load
 // ahead of the stores.  The source starts at any element (4-byte alignment, which
-// is all a 16-byte load needs), the slot at a 16-byte boundary; the last lane in
-// the row takes a remainder of up to three elements.
+// is all a 16-byte load needs), the slot at a 16-byte boundary; a remainder of up
+// to three elements goes to the first lanes, one each.
 template <int NT, int U>
 __device__ inline void copy_ragged(const IngestArgs& a, int64_t j, int tid) {
     typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));

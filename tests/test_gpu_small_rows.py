@@ -222,6 +222,9 @@ def test_update_ingest_ragged_rows(max_len, n_update, aux, given):
             length[20] = max_len + 3  # stored truncated
         offsets = np.concatenate([[0], np.cumsum(length)])
         total = int(offsets[-1])
+        if bad:  # beyond the source's end and before its start: both rows beside each are stored empty
+            offsets[40], offsets[60] = total + 9, -1
+            length[[39, 40, 59, 60]] = 0
         tok = rng.integers(0, 1 << 30, total).astype(np.int32)
         rows = dict(offsets=dev(offsets), action=dev(rng.integers(0, 256, (n, 4), dtype=np.uint8)),
                     reward=dev(rng.standard_normal(n).astype(np.float32)))
@@ -260,6 +263,36 @@ def test_update_ingest_ragged_rows(max_len, n_update, aux, given):
         assert info.size == min(cap, (it + 1) * n)
     for b in bufs:
         b.close()
+
+
+# variable-length rows around the most that take one launch, against the two calls
+@pytest.mark.parametrize("n", [1024, 1025])
+def test_update_ingest_ragged_limit(n):
+    print(f"ragged update_ingest rows n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    cap, max_len = 1500, 12
+    length = rng.integers(0, max_len + 1, n)
+    offsets = np.concatenate([[0], np.cumsum(length)])
+    tok = dev(rng.integers(0, 1 << 30, int(offsets[-1])).astype(np.int32))
+    rows = dict(offsets=dev(offsets), reward=dev(rng.standard_normal(n).astype(np.float32)))
+    idx, prio = dev(rng.integers(0, n, 200)), dev(synth.quantise_priority(rng.lognormal(0, 2, 200)))
+    got = []
+    for one in (True, False):
+        buf = cd.ReplayBuffer(cap, (max_len,), torch.int32, ragged=True)
+        buf.ingest(tok, **rows)
+        if one:
+            buf.update_ingest(idx, prio, tok, **rows)
+        else:
+            buf.update(idx, prio)
+            buf.ingest(tok, **rows)
+        assert buf.sync_check() == cd.OK, cd.last_error()
+        tree_consistent(buf, cap)
+        lens = read_col(buf, cd.COL_LENGTH, cap * 4, np.int32)
+        seq = read_col(buf, cd.COL_OBS, cap * max_len * 4, np.int32).reshape(cap, max_len)
+        got.append((lens, np.where(np.arange(max_len) < lens[:, None], seq, -1), read_col(buf, cd.COL_REWARD, cap * 4, np.uint32),
+                    read_col(buf, cd.COL_LEAVES, cap * 4, np.uint32)))
+        buf.close()
+    assert all(np.array_equal(x, y) for x, y in zip(*got))
 
 
 # token delivery with advantages at each width it is dispatched on (256, 512 and

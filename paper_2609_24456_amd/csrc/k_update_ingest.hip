@@ -67,11 +67,12 @@ __global__ __launch_bounds__(kUpdateThreads) void k_update_ingest(UpdateArgs u, 
     __shared__ uint32_t keys[kTable];
     __shared__ int32_t owner[kTable];
     __shared__ unsigned long long bins[kBins];
-    if (blockIdx.x < (uint32_t)groups) {
+    const uint32_t first = SPLIT > 0 ? (uint32_t)groups : 1u;  // the first ingest block
+    if (blockIdx.x < first) {
         // one workgroup's atomics cost less than waiting for the stored maximum
         const uint32_t seen = SPLIT > 0 ? u.state->max_prio : 0u;
         uint32_t pmax;
-        if constexpr (SPLIT > 0) pmax = update_part<SPLIT>(u, blockIdx.x, (uint32_t)groups, keys, owner, bins, a.head, a.n);
+        if constexpr (SPLIT > 0) pmax = update_part<SPLIT>(u, blockIdx.x, first, keys, owner, bins, a.head, a.n);
         else pmax = update_pass(u, keys, owner, bins, a.head, a.n);
         flush_bins(u.tree, bins);
         raise_max(u.state, seen, pmax);
@@ -80,28 +81,24 @@ __global__ __launch_bounds__(kUpdateThreads) void k_update_ingest(UpdateArgs u, 
     if constexpr (std::is_same<V, Ragged>::value) {
         // whole workgroups of metadata, then one per sequence
         const int64_t meta_wgs = (meta_subs + kSubs - 1) / kSubs;
-        const int64_t j = (int64_t)(blockIdx.x - (uint32_t)groups) - meta_wgs;
+        const int64_t j = (int64_t)(blockIdx.x - first) - meta_wgs;
         if (j >= 0) {
             copy_ragged<kUpdateThreads, 1>(a, j, threadIdx.x);
             return;
         }
     }
-    const int64_t sub0 = (int64_t)(blockIdx.x - (uint32_t)groups) * kSubs;
+    const int64_t sub0 = (int64_t)(blockIdx.x - first) * kSubs;
     const int64_t sub = sub0 + threadIdx.x / kIngestThreads;
     const int tid = (int)(threadIdx.x % kIngestThreads);
     RaiseList raise{u.idx, u.prio, u.n, u.size};
     if constexpr (SPLIT > 0) {
-        if (sub0 < meta_subs && !a.src_prio) {  // uniform: a long list is read by the whole workgroup
-            raise.known = list_max(raise, owner);
-            raise.n = 1;
-            raise.idx = nullptr;
-        }
+        if (sub0 < meta_subs && !a.src_prio) raise.known = list_max(raise, owner);  // uniform: read by the whole workgroup
     }
     if (sub < meta_subs) {
         // the update block may already have raised the stored maximum with the
         // same priorities: raised_max takes max() over both, so the order of
         // the two parts does not matter
-        ingest_meta(a, sub, tid, raise);
+        ingest_meta<SPLIT == 0 ? kRaiseRead : kRaiseKnown>(a, sub, tid, raise);
     } else if constexpr (!std::is_same<V, Ragged>::value) {
         if (sub - meta_subs < copy_subs) copy_dense<V>(a, sub - meta_subs, tid);
     }

@@ -37,7 +37,7 @@ __global__ __launch_bounds__(kThreads) void k_sample(SampleArgs a, DivB dv) {
         }
     }
     // buffer-wide normalisation: this workgroup's share of the leaf minimum
-    if (a.leaf_min) fold_leaf_min<kThreads>(a, blockIdx.x, gridDim.x);
+    if (a.leaf_min) fold_leaf_min<kThreads, true>(a, blockIdx.x, gridDim.x);
 }
 
 constexpr int kWThreads = 1024;

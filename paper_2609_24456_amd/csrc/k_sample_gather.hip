@@ -66,7 +66,7 @@ __device__ void sampler_wg(const SampleArgs& sa, const DivB& dv, int64_t wg) {
     if (!sa.w_out) return;  // kernel argument: uniform
     // buffer-wide normalisation: this workgroup's share of the leaf minimum,
     // folded in before the ticket like the parked leaves
-    if (sa.leaf_min) fold_leaf_min<NT>(sa, wg, (sa.batch + kPer - 1) / kPer);
+    if (sa.leaf_min) fold_leaf_min<NT, false>(sa, wg, (sa.batch + kPer - 1) / kPer);
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     __builtin_amdgcn_s_waitcnt(0);  // this wavefront's parked leaves are acknowledged
     __syncthreads();                // ... and every wavefront's
@@ -241,7 +241,7 @@ __global__ __launch_bounds__(kWg) void k_sample_rows(SampleArgs sa, GatherArgs a
         row.load(a, d.slot, units, by_units);
         row.store(a, k, lut);
     }
-    if (!TICKET && sa.leaf_min) fold_leaf_min<kWg>(sa, wg, row_wgs);  // buffer-wide normalisation
+    if (!TICKET && sa.leaf_min) fold_leaf_min<kWg, true>(sa, wg, row_wgs);  // buffer-wide normalisation
 }
 
 template <int XF>

@@ -933,16 +933,18 @@ __device__ __forceinline__ double get_f64(uint64_t* p) {
 // Replays one lane's chunk from A (at its end) and stores A_t and R_t.  The
 // rows leave without staying dirty in the L2s for the end-of-kernel write-back:
 // through write-through buffer stores at agent scope (8.9 -> 8.7 us on
-// [2048, 256]) where the byte offsets fit a buffer store and the outputs are
-// below kGaeStreamElems each, non-temporally beyond ([4096, 2048] 45.5 -> 40.6
-// us, [256, 32768] truncated 53 -> 49 us; [256, 16384] 18.3 -> 19.0 us).
+// [2048, 256]) where the byte offsets fit a buffer store, and non-temporally for
+// outputs of kGaeStreamElems and more ([4096, 2048] 45.5 -> 40.6 us, [256, 32768]
+// truncated 53 -> 49 us; [256, 16384] 18.3 -> 19.0 us) whose rows are whole cache
+// lines, so that a tile's 32 environments are one (otherwise each of its stores
+// leaves two lines partly written: [256, 33000] 52.6 us non-temporally).
 constexpr int64_t kGaeStreamElems = 8ll << 20;
 
 template <bool TRUNC, int L, bool V4>
 __device__ __forceinline__ void replay(const GaeArgs& a, const SegChunk<TRUNC, L, V4>& ch, double (&A)[kV], double gl,
                                        int64_t t0, int64_t e0, bool active) {
     const int64_t T = a.T, E = a.E;
-    const bool wt = T * E < kGaeStreamElems;  // uniform
+    const bool wt = T * E < kGaeStreamElems || (E % kSegEnvs != 0 && T * E * 4 <= 0x7fffffffll);  // uniform
     const int nrec = wt ? (int)(T * E * 4) : 0;
     const __amdgpu_buffer_rsrc_t rsa = __builtin_amdgcn_make_buffer_rsrc(a.adv, 0, nrec, kRsrcRaw32);
     const __amdgpu_buffer_rsrc_t rsr = __builtin_amdgcn_make_buffer_rsrc(a.ret, 0, nrec, kRsrcRaw32);

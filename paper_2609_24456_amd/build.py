@@ -2,6 +2,7 @@
 import concurrent.futures as cf
 import os
 import subprocess
+import warnings
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -34,7 +35,7 @@ def _compile(src, verbose):
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
-        check = ex.submit(build_tensor_check, verbose)
+        check = ex.submit(try_tensor_check, verbose)
         objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
         check.result()
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", LIB + ".tmp"] + objs
@@ -48,7 +49,8 @@ def build(verbose: bool = False) -> str:
 
 
 # The binding's native argument check (csrc/tensor_check.cpp), a CPython module
-# against the installed torch.
+# against the installed torch, whose version it carries.  The binding works without
+# it (the same checks in Python, slower), so the build does too.
 TENSOR_CHECK = os.path.join(PKG, "_tensor_check.so")
 
 
@@ -60,7 +62,7 @@ def build_tensor_check(verbose: bool = False) -> str:
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     inc = ext.include_paths() + [sysconfig.get_paths()["include"], "/opt/rocm/include"]
     cmd = (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__=1",
-            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DTORCH_VERSION_BUILT="{torch.__version__}"']
            + [x for i in inc for x in ("-isystem", i)]
            + [os.path.join(CSRC, "tensor_check.cpp"), "-o", TENSOR_CHECK + ".tmp", "-L" + lib, "-ltorch_python", "-ltorch",
               "-ltorch_cpu", "-lc10", "-Wl,-rpath," + lib])
@@ -71,6 +73,17 @@ def build_tensor_check(verbose: bool = False) -> str:
         raise RuntimeError(f"g++ failed for tensor_check.cpp:\n{r.stderr}")
     os.replace(TENSOR_CHECK + ".tmp", TENSOR_CHECK)
     return TENSOR_CHECK
+
+
+def try_tensor_check(verbose: bool = False):
+    """build_tensor_check(); where it fails, a warning, and no module of an earlier build stays."""
+    try:
+        return build_tensor_check(verbose)
+    except (ImportError, OSError, RuntimeError) as e:
+        warnings.warn(f"no native argument check, the binding checks in Python: {e}")
+        if os.path.exists(TENSOR_CHECK):
+            os.remove(TENSOR_CHECK)
+        return None
 
 
 # The ABI's host code (api.hip: argument checks, layouts, ring state,

@@ -13,11 +13,18 @@ import torch
 from .abi import *  # noqa: F401,F403  (status codes, enums, structs, SIGNATURES)
 from .abi import _STATUS_NAMES, load as _load_abi  # noqa: F401
 
-try:  # built beside libconduit.so; without it every check below runs in Python
-    from ._tensor_check import address as _address
+try:  # built beside libconduit.so; without it, or for another torch, every check below runs in Python
+    from . import _tensor_check
+    if getattr(_tensor_check, "torch_version", None) != torch.__version__:
+        raise ImportError("built against another torch")
+    _address = _tensor_check.address
 except ImportError:
     def _address(t, dtype, nbytes, numel):
         return None
+
+# torch's own short way to the current stream's handle, where this torch has it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libconduit.so")
 _lib = None
@@ -46,8 +53,8 @@ def _check(status):
 
 def _stream(stream):
     if stream is None:
-        if torch.cuda.is_initialized():  # the current stream's handle without a Stream object around it
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _raw_stream and _current_device and torch.cuda.is_initialized():  # no Stream object around the handle
+            return _raw_stream(_current_device())
         return C.c_void_p(torch.cuda.current_stream().cuda_stream)
     if isinstance(stream, torch.cuda.Stream):
         return C.c_void_p(stream.cuda_stream)

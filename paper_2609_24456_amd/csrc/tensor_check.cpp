@@ -16,7 +16,7 @@ bool dtype_is(PyObject* want, at::ScalarType have) {
     return THPDtype_Check(want) && reinterpret_cast<THPDtype*>(want)->scalar_type == have;
 }
 
-// A size in bytes or elements: None (no requirement), or an int; -1 on anything else
+// A size in bytes or elements: None (no requirement, 0) or an int; false on anything else
 bool read_size(PyObject* o, long long* n) {
     if (o == Py_None) {
         *n = 0;
@@ -75,4 +75,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_tensor_check", "checks of the bin
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__tensor_check(void) { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__tensor_check(void) {
+    PyObject* m = PyModule_Create(&module);
+    // the layouts read above are this torch's: the binding uses no other's
+    if (m && PyModule_AddStringConstant(m, "torch_version", TORCH_VERSION_BUILT) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -1,5 +1,9 @@
 """The binding's native argument check: it accepts exactly what the Python checks
 accept, and leaves everything else (with the error to raise) to them."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -16,6 +20,39 @@ def test_left_to_python_on_the_host():
         _tensor_check.address(t)
     with pytest.raises(ValueError, match="on a HIP device"):
         cd._ptr(t, torch.float32, "t")
+
+
+def test_build_without_it(tmp_path, monkeypatch):
+    from paper_2609_24456_amd import build as B
+    old = tmp_path / "_tensor_check.so"
+    old.write_bytes(b"an earlier build's")
+    monkeypatch.setattr(B, "TENSOR_CHECK", str(old))
+    monkeypatch.setattr(B, "CSRC", str(tmp_path))  # no source: the compiler fails
+    with pytest.warns(UserWarning, match="checks in Python"):
+        assert B.try_tensor_check() is None
+    assert not old.exists()
+
+
+@pytest.mark.parametrize("version", [None, "0.1"])
+def test_module_of_another_torch_is_not_used(version):
+    prog = f"""
+import sys, types
+m = types.ModuleType("paper_2609_24456_amd._tensor_check")
+m.address = lambda *a: 1 / 0
+if {version!r}: m.torch_version = {version!r}
+sys.modules[m.__name__] = m
+import paper_2609_24456_amd
+from paper_2609_24456_amd import conduit as cd
+assert cd._address(None, None, None, None) is None
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", prog], cwd=root, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr[-2000:]
+
+
+def test_module_in_use_is_of_this_torch():
+    assert _tensor_check.torch_version == torch.__version__
+    assert cd._address is _tensor_check.address
 
 
 @pytest.mark.gpu

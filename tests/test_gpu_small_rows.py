@@ -333,3 +333,63 @@ def test_sample_pack_gae_widths(max_len, B, values):
         else:
             assert torch.equal(x, y)
     buf.close()
+
+
+# batches whose weights take two launches of their own: captured, replayed with new
+# uniforms and priorities and eager calls between; then a tree of zeros
+@pytest.mark.parametrize("norm", [0, 1])
+def test_large_batch_weights_captured(norm):
+    print(f"captured weights norm={norm}", flush=True)
+    rng = np.random.default_rng(norm)
+    cap, B = 3000, 2049
+    obs = rng.standard_normal((cap, 8)).astype(np.float32)
+    prio = synth.quantise_priority(rng.lognormal(0, 1, cap))
+    buf = cd.ReplayBuffer(cap, (8,), torch.float32, action_bytes=0, weight_norm=norm)
+    orc = oracle.Replay(cap, (8,), np.float32, act_bytes=0)
+    buf.ingest(dev(obs), prio=dev(prio))
+    orc.ingest(cap, obs=obs, prio=prio)
+    u, p = dev(synth.uniforms(rng, B)), dev(prio[:B].copy())
+    idx, w = torch.empty(B, dtype=torch.int64, device="cuda"), torch.empty(B, device="cuda")
+    idx2, w2, out = torch.empty_like(idx), torch.empty_like(w), torch.empty((B, 1, 8), device="cuda")
+    xf = cd.transform(cd.XF_NONE)
+
+    def step():
+        buf.sample_gather(u, xf, idx_out=idx, w_out=w, obs=out)
+        buf.sample(u, idx2, w2)
+        buf.update(idx, p)
+
+    def check(uniforms, new):
+        o_idx, o_w = orc.sample(uniforms, buffer_norm=bool(norm))
+        assert np.array_equal(host(idx), o_idx) and np.array_equal(host(idx2), o_idx)
+        assert_weights_close(host(w), o_w)
+        assert torch.equal(w, w2) and np.array_equal(host(out)[:, 0], obs[o_idx])
+        orc.update(o_idx, new)
+
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        step()
+    torch.cuda.current_stream().wait_stream(s)
+    torch.cuda.synchronize()
+    check(host(u, np.uint64), host(p, np.uint32))
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        step()
+    for _ in range(4):
+        uniforms, new = synth.uniforms(rng, B), synth.quantise_priority(rng.lognormal(0, 2, B))
+        u.copy_(dev(uniforms))
+        p.copy_(dev(new))
+        g.replay()
+        torch.cuda.synchronize()
+        check(uniforms, new)
+        few = rng.integers(0, cap, 5)
+        buf.update(dev(few), dev(np.full(5, 77, np.uint32)))
+        orc.update(few, np.full(5, 77, np.uint32))
+    assert buf.sync_check() == cd.OK, cd.last_error()
+    buf.update(torch.arange(cap, device="cuda"), torch.zeros(cap, dtype=torch.int32, device="cuda"))
+    for call in (lambda: buf.sample_gather(u, xf, idx_out=idx, w_out=w, obs=out), lambda: buf.sample(u, idx, w)):
+        call()
+        assert buf.sync_check() == cd.ESTATE
+        buf.clear_error()
+        assert (host(idx) == -1).all() and not host(w).any() and not host(out).any()
+    buf.close()

@@ -531,7 +531,8 @@ __device__ __forceinline__ UnionItem union_item(const GatherArgs& a, const Union
     return t;
 }
 
-template <int XF>
+// NT as in issue().
+template <int XF, bool NT>
 __device__ __forceinline__ void union_issue(const GatherArgs& a, const UnionItem& t, typename UnitOf<XF>::T (&v)[kUnroll],
                                             int32_t& sj, uint32_t& ej, int tid) {
     typedef typename UnitOf<XF>::T U;
@@ -541,7 +542,9 @@ __device__ __forceinline__ void union_issue(const GatherArgs& a, const UnionItem
 #pragma unroll
     for (int r = 0; r < kUnroll; ++r) {
         const int64_t u = u0 + (int64_t)r * kThreads;
-        v[r] = src[u < units ? u : units - 1];
+        const int64_t uc = u < units ? u : units - 1;
+        if constexpr (NT) v[r] = __builtin_nontemporal_load(src + uc);
+        else v[r] = src[uc];
     }
     if (a.stack > 1) {  // kernel argument: uniform
         sj = a.step[t.src];
@@ -582,7 +585,7 @@ __device__ __forceinline__ void union_finish(const GatherArgs& a, const UnionRow
 // sample's slot; run() needs the bootstrap slot too (r.jn) and finishes the
 // items.  The first group also writes the state row's scalar columns, after
 // the frames.
-template <int XF>
+template <int XF, bool NT>
 struct UnionGather {
     typename UnitOf<XF>::T va[kUnroll], vb[kUnroll];
     int32_t sja, sjb;
@@ -598,7 +601,7 @@ struct UnionGather {
         if (part == 0) rs = row_scalars_load(a, r.i, tid);
         if (part < items) {
             ta = union_item(a, r, part, bpf);
-            union_issue<XF>(a, ta, va, sja, eja, tid);
+            union_issue<XF, NT>(a, ta, va, sja, eja, tid);
         }
     }
 
@@ -609,13 +612,13 @@ struct UnionGather {
             const bool has_b = it + parts < items;  // uniform
             if (has_b) {
                 tb = union_item(a, r, it + parts, bpf);
-                union_issue<XF>(a, tb, vb, sjb, ejb, tid);
+                union_issue<XF, NT>(a, tb, vb, sjb, ejb, tid);
             }
             union_finish<XF>(a, r, ta, va, sja, eja, next_out, lut, tid);
             if (!has_b) break;
             if (it + 2 * parts < items) {
                 ta = union_item(a, r, it + 2 * parts, bpf);
-                union_issue<XF>(a, ta, va, sja, eja, tid);
+                union_issue<XF, NT>(a, ta, va, sja, eja, tid);
             }
             union_finish<XF>(a, r, tb, vb, sjb, ejb, next_out, lut, tid);
         }

@@ -34,6 +34,8 @@
 // call.  No workgroup waits for another, no release fence (which would write
 // back the L2 under the frame stores) is needed, and the ticket latency stays
 // off the frame workgroups.
+#include <type_traits>
+
 #include "descend.h"
 #include "gae_packed_dev.h"
 #include "gather_dev.h"
@@ -311,7 +313,16 @@ hipError_t launch_xf(const SampleArgs& sa, const GatherArgs& ga, hipStream_t s, 
 // second barrier, with the bootstrap slot known, they convert and store every
 // frame once into the stacks it belongs to.  Sampler workgroups as in
 // k_sample_gather.
-template <int XF, int PRE, int DEPTH, bool SHARED>
+//
+// NT: frames of a ring beyond the last-level cache come from HBM and are not read
+// again soon; loaded non-temporally they leave that cache to the outputs (steps in
+// turn on three replays: 512 samples of four 84x84 frames, 3 steps, out of 200,000
+// 41.3 -> 39.7 us; 8,192 single 48x48 frames out of 160,000 150.7 -> 115.1).  A ring
+// the cache holds is read through it (8,192 of 50,000: 117 us, 136
+// non-temporally).
+constexpr int64_t kNtMinRing = 256ll << 20;
+
+template <int XF, int PRE, int DEPTH, bool SHARED, bool NT>
 __global__ __launch_bounds__(kWg) void k_sample_gather_nstep(SampleArgs sa, GatherArgs a, NstepArgs na,
                                                              void* next_out, DivB dv, int32_t bpf,
                                                              int32_t gather_wgs, int32_t log2_wgs) {
@@ -337,7 +348,7 @@ __global__ __launch_bounds__(kWg) void k_sample_gather_nstep(SampleArgs sa, Gath
     UnionRow r = union_row(a, b, s_slot, na.n, next_out != nullptr);
     const int half = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kThreads));
     const int part = sub * 2 + half, tid = (int)(threadIdx.x % kThreads);
-    UnionGather<XF> g;
+    UnionGather<XF, NT> g;
     g.start(a, r, part, bpf, tid);  // the first frames' loads, while the window is evaluated
     if (threadIdx.x < kWave) {
         const int64_t next = nstep_window_finish(na, b, win, sub == 0);
@@ -363,12 +374,15 @@ struct FusedNstepLaunch {
         const int64_t frames = ga.stack + (next_out ? (na.n < ga.stack ? na.n : ga.stack) : 0);
         const int32_t l = log2_wgs_per_sample(sa.batch, bpf * frames, XF == CONDUIT_XF_U8_BF16_NORM);
         const dim3 grid((unsigned)(sampler_wgs + (sa.batch << l))), block(kWg);
-        if (l)
-            hipLaunchKernelGGL((k_sample_gather_nstep<XF, PRE, DEPTH, true>), grid, block, 0, s, sa, ga, na, next_out, dv,
-                               (int32_t)bpf, (int32_t)(sa.batch << l), l);
-        else
-            hipLaunchKernelGGL((k_sample_gather_nstep<XF, PRE, DEPTH, false>), grid, block, 0, s, sa, ga, na, next_out, dv,
-                               (int32_t)bpf, (int32_t)sa.batch, 0);
+        auto go = [&](auto shared, auto nt) {
+            hipLaunchKernelGGL((k_sample_gather_nstep<XF, PRE, DEPTH, shared.value, nt.value>), grid, block, 0, s, sa, ga,
+                               na, next_out, dv, (int32_t)bpf, (int32_t)(sa.batch << l), l);
+        };
+        const std::true_type yes;
+        const std::false_type no;
+        if (l) go(yes, no);
+        else if (ga.limit * ga.row_bytes > kNtMinRing) go(no, yes);
+        else go(no, no);
         return hipGetLastError();
     }
 };

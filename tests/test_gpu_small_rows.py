@@ -393,3 +393,32 @@ def test_large_batch_weights_captured(norm):
         buf.clear_error()
         assert (host(idx) == -1).all() and not host(w).any() and not host(out).any()
     buf.close()
+
+
+# n-step delivery out of a ring beyond the last-level cache (256 MiB) and just below
+# it, against the two calls it stands for
+@pytest.mark.parametrize("cap", [38000, 38100])
+def test_nstep_of_a_large_ring(cap):
+    print(f"n-step large ring cap={cap}", flush=True)
+    rng = np.random.default_rng(cap)
+    done = (rng.random(cap) < 0.02).astype(np.uint8)
+    episode, step = synth.episodes_from_done(done)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(cap)
+    obs = torch.randint(-2 ** 31, 2 ** 31, (cap, 1764), generator=g, device="cuda", dtype=torch.int32).view(torch.uint8)
+    buf = cd.ReplayBuffer(cap, (84, 84), torch.uint8, frame_stack=2)
+    buf.ingest(obs.view(cap, 84, 84), reward=dev(rng.standard_normal(cap).astype(np.float32)), done=dev(done),
+               episode_id=dev(episode), step=dev(step), prio=dev(synth.quantise_priority(rng.lognormal(0, 1, cap))))
+    B, n, xf = 300, 3, cd.transform(cd.XF_U8_F32)
+    u = dev(synth.uniforms(rng, B))
+    new = lambda: torch.full((B, 2, 84, 84), 7.0, device="cuda")  # noqa: E731
+    one, nxt = new(), new()
+    idx, w, ni, ret, disc, valid = buf.sample_gather_nstep(u, xf, n, 0.9, next_obs=nxt, obs=one)
+    two, nxt2 = new(), new()
+    idx2, w2 = buf.sample_gather(u, xf, obs=two)
+    ni2, ret2, disc2, valid2 = (torch.empty_like(x) for x in (ni, ret, disc, valid))
+    cd.conduit_nstep(buf.handle, idx2, B, n, 0.9, ni2, ret2, disc2, valid2, xf, nxt2)
+    assert buf.sync_check() == cd.OK, cd.last_error()
+    for x, y in ((idx, idx2), (w, w2), (one, two), (nxt, nxt2), (ni, ni2), (ret, ret2), (disc, disc2), (valid, valid2)):
+        assert torch.equal(x, y)
+    buf.close()

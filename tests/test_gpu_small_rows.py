@@ -417,7 +417,7 @@ def test_nstep_of_a_large_ring(cap):
     two, nxt2 = new(), new()
     idx2, w2 = buf.sample_gather(u, xf, obs=two)
     ni2, ret2, disc2, valid2 = (torch.empty_like(x) for x in (ni, ret, disc, valid))
-    cd.conduit_nstep(buf.handle, idx2, B, n, 0.9, ni2, ret2, disc2, valid2, xf, nxt2)
+    cd.conduit_nstep(buf.handle, idx2, n, 0.9, ni2, ret2, disc2, valid2, xf, nxt2)
     assert buf.sync_check() == cd.OK, cd.last_error()
     for x, y in ((idx, idx2), (w, w2), (one, two), (nxt, nxt2), (ni, ni2), (ret, ret2), (disc, disc2), (valid, valid2)):
         assert torch.equal(x, y)

@@ -46,7 +46,10 @@ constexpr int64_t kPipeMaxOutBytes = 128ll << 20;
 //         more loads in flight (566 84x84 frames of 60,941 5.8 us, 7.1 flat; 2,267
 //         14.9, 18.3; of 2,264 and 9,068 in the last-level cache 5.6, 4.6 and 13.1,
 //         13.6);
-//       - such frames of a sampled batch, whose rows are in address order (a
+//       - rows of 4-byte units that fill half of their items, into more than
+//         kPipeMaxOutBytes (57,429 rows of 1,023 floats 96.2 us, 108.8 flat; of 601
+//         floats, a third, 134.7 and 110);
+//       - frames to fp32 of a sampled batch that fill their items, whose rows are in address order (a
 //         step of 302 4x120x120 25.6 us, 27.1 flat; of 820 3x224x224 107.8, 115.9);
 //   * single frames of up to kFlatMaxNormUnits units normalised to bf16 (4,096
 //     64x64 frames 15.3 -> 11.8 us); larger ones spend more on finding each
@@ -261,7 +264,8 @@ hipError_t launch_gather_xf(const GatherArgs& a, hipStream_t s, int64_t tail_blo
     const bool norm = XF == CONDUIT_XF_U8_BF16_NORM;
     // frames to fp32 that fill at least 3/4 of their items
     const bool full = XF == CONDUIT_XF_U8_F32 && units * 4 >= bpf * kUnitsPerBlock * 3;
-    const bool items = full && (a.weights.w || (a.limit * a.row_bytes > kFlatMaxSource && out_bytes <= kPipeMaxOutBytes));
+    const bool rows4 = XF == CONDUIT_XF_NONE && units * 2 >= bpf * kUnitsPerBlock && out_bytes > kPipeMaxOutBytes;
+    const bool items = rows4 || (full && (a.weights.w || (a.limit * a.row_bytes > kFlatMaxSource && out_bytes <= kPipeMaxOutBytes)));
     const bool flat = units <= kFlatMaxUnits || (a.stack == 1 && !items && (!norm || units <= kFlatMaxNormUnits));
     const int64_t total = a.n * a.stack * units;
     if (n_items > 0 && flat && total < (1ll << 31) - kThreads * kFlatUnroll) {

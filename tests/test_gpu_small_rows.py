@@ -69,6 +69,22 @@ def test_minibatch_source_sizes(units, n, beyond):
     assert np.array_equal(host(out), host(src[perm]).astype(np.float32) / np.float32(255))
 
 
+# rows of 4-byte units around half an item (896 units), into outputs around 128 MiB
+@pytest.mark.parametrize("units", [895, 897])
+@pytest.mark.parametrize("beyond", [False, True])
+def test_minibatch_wide_vectors(units, beyond):
+    print(f"wide vectors units={units} beyond={beyond}", flush=True)
+    n = (128 << 20) // (units * 4) + (1 if beyond else 0)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(units)
+    src = torch.randint(-2 ** 31, 2 ** 31, (n + 7, units), generator=g, device="cuda", dtype=torch.int32)
+    perm = torch.randperm(n + 7, generator=g, device="cuda")[:n]
+    out = torch.zeros((n, units), dtype=torch.int32, device="cuda")
+    cd.conduit_minibatch_gather(src, units * 4, n + 7, perm, cd.transform(cd.XF_NONE), out)
+    assert cd.conduit_sync_check() == cd.OK, cd.last_error()
+    assert torch.equal(out, src[perm])
+
+
 # columns alone: rows of 0 bytes, with and without an output pointer, under every transform
 @pytest.mark.parametrize("kind", [cd.XF_NONE, cd.XF_U8_F32, cd.XF_U8_BF16_NORM])
 @pytest.mark.parametrize("pointer", [False, True])

@@ -8,7 +8,8 @@ namespace conduit {
 enum GaePath : int32_t {
     GAE_ONE_PASS = 0,        // one environment per lane, all T steps per workgroup
     GAE_ONE_PASS_V4 = 1,     // four environments per lane, all T steps per workgroup
-    GAE_SHORT = 2,           // T <= 64: one tile of 32 environments per workgroup
+    GAE_SHORT = 2,           // one tile holds all steps: T <= 64, up to 256 where enough environments
+                             // (32 per workgroup; 32 or 16 per wavefront for T <= 16 or 32)
     GAE_LOOK_BACK = 3,       // split along T, one launch, look-back over segment maps
     GAE_THREE_LAUNCHES = 4,  // split along T, fold / carry / replay launches
 };
@@ -16,7 +17,7 @@ enum GaePath : int32_t {
 struct GaePlan {
     int32_t path;      // GaePath
     int32_t chunk;     // steps per lane of a tile (0 for the one-pass kernels)
-    int64_t groups;    // tiles across E (32 environments each)
+    int64_t groups;    // groups of 32 environments
     int64_t segments;  // tiles along T
 };
 

@@ -1330,7 +1330,9 @@ GaePlan plan_gae(int64_t T, int64_t E, bool vec) {
         // one segment of longer chunks spares the look-back: up to 128 steps for
         // every whole group of environments ([128, 64] 5.8 -> 5.0 us, [128, 4096]
         // 7.2 -> 5.8, [128, 16384] 13.9 -> 9.4), up to 256 where half the compute
-        // units get a tile ([256, 4096] 9.3 -> 8.7, [256, 1024] 7.2 -> 7.9)
+        // units get a tile ([256, 4096] 9.3 -> 8.7, [256, 1024] 7.2 -> 7.9).  A tile
+        // needs no table, but beyond the table's size such rollouts still take the
+        // one-pass kernels ([128, 65536] 27 us, [128, 65568] 154; truncated 38, 390)
         if (T <= (int64_t)kSegChunks * 4 && E >= kSegEnvs) return GaePlan{GAE_SHORT, 4, groups, 1};
         if (T <= (int64_t)kSegChunks * 8 && groups >= kGaeSplitMinTiles / 2) return GaePlan{GAE_SHORT, 8, groups, 1};
         return GaePlan{GAE_LOOK_BACK, L, groups, segs};

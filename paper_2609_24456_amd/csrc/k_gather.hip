@@ -41,16 +41,17 @@ constexpr int64_t kPipeMaxOutBytes = 128ll << 20;
 //     items with a remainder, and large outputs leave faster (88x88 50 -> 32 us;
 //     65,536 rows of 4 KB 114 -> 98 us; 16,384 images of 3x84x84 to fp32 322 -> 310
 //     us), except
-//       - frames to fp32 that fill their items and come from HBM (a source beyond
-//         kFlatMaxSource) into up to kPipeMaxOutBytes: the persistent kernel has
-//         more loads in flight (566 84x84 frames of 60,941 5.8 us, 7.1 flat; 2,267
-//         14.9, 18.3; of 2,264 and 9,068 in the last-level cache 5.6, 4.6 and 13.1,
-//         13.6);
+//       - frames to fp32 that fill their items, from HBM (a source beyond
+//         kFlatMaxSource) or of a sampled batch, into up to kItemsMaxOutBytes: the
+//         persistent kernel has more loads in flight (566 84x84 frames of 60,941 5.8
+//         us, 7.1 flat; 2,267 14.9, 18.3; 2,900 25.0, 22.5; 566 of 2,264 in the last-level
+//         cache 5.6, 4.6; a step of 216 sampled 3x152x152 23.0, 26.3, of 324 33.9, 33.1);
 //       - rows of 4-byte units that fill half of their items, into more than
 //         kPipeMaxOutBytes (57,429 rows of 1,023 floats 96.2 us, 108.8 flat; of 601
 //         floats, a third, 134.7 and 110);
-//       - frames to fp32 of a sampled batch that fill their items, whose rows are in address order (a
-//         step of 302 4x120x120 25.6 us, 27.1 flat; of 820 3x224x224 107.8, 115.9);
+//       - such frames of a sampled batch into more than kPipeMaxOutBytes, its rows in
+//         address order (a step of 694 4x120x120 46.1 us, 48.8 flat; 498 3x224x224
+//         73.3, 77.7);
 //   * single frames of up to kFlatMaxNormUnits units normalised to bf16 (4,096
 //     64x64 frames 15.3 -> 11.8 us); larger ones spend more on finding each
 //     unit's row than they save (1,024 images of 3x224x224: 83 us as items, 98
@@ -61,6 +62,7 @@ constexpr int64_t kPipeMaxOutBytes = 128ll << 20;
 constexpr int64_t kFlatMaxUnits = 512;
 constexpr int64_t kFlatMaxNormUnits = 1024;
 constexpr int64_t kFlatMaxSource = 256ll << 20;
+constexpr int64_t kItemsMaxOutBytes = 64ll << 20;
 constexpr int kFlatUnroll = 4;         // its most units per lane
 constexpr int64_t kFlatWgsPerCu = 4;   // workgroups per compute unit before a lane takes more units
 constexpr int64_t kFlatLoopWgs = 16;   // bf16: workgroups per compute unit, each looping with its table
@@ -265,7 +267,9 @@ hipError_t launch_gather_xf(const GatherArgs& a, hipStream_t s, int64_t tail_blo
     // frames to fp32 that fill at least 3/4 of their items
     const bool full = XF == CONDUIT_XF_U8_F32 && units * 4 >= bpf * kUnitsPerBlock * 3;
     const bool rows4 = XF == CONDUIT_XF_NONE && units * 2 >= bpf * kUnitsPerBlock && out_bytes > kPipeMaxOutBytes;
-    const bool items = rows4 || (full && (a.weights.w || (a.limit * a.row_bytes > kFlatMaxSource && out_bytes <= kPipeMaxOutBytes)));
+    const bool sampled = a.weights.w != nullptr;
+    const bool few = out_bytes <= kItemsMaxOutBytes && (sampled || a.limit * a.row_bytes > kFlatMaxSource);
+    const bool items = rows4 || (full && (few || (sampled && out_bytes > kPipeMaxOutBytes)));
     const bool flat = units <= kFlatMaxUnits || (a.stack == 1 && !items && (!norm || units <= kFlatMaxNormUnits));
     const int64_t total = a.n * a.stack * units;
     if (n_items > 0 && flat && total < (1ll << 31) - kThreads * kFlatUnroll) {

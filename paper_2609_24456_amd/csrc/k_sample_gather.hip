@@ -483,7 +483,9 @@ hipError_t launch_sample_gather_nstep(const SampleArgs& sa, const GatherArgs& ga
         bpf * frames > kFusedNstepMaxItemsPerRow)
         return hipErrorNotSupported;
     // large batches of small rows: the wavefront-per-sample delivery, then the
-    // targets and the flat gather
+    // targets and the flat gather (a step of 1,025 rows of 8 floats, n = 3, 25.0 us
+    // in one launch and 23.3 in these, 2,048 39.6 and 23.2, 16,384 303 and 38.8; of
+    // 240 floats 25.4 and 24.0, 40.6 and 24.2, 310 and 45)
     if (units * ga.stack <= kRowMaxUnits && sa.batch > kRowsTicketMax) return hipErrorNotSupported;
     if (c16) return launch_nstep_xf<kXfCopy16>(sa, ga, na, next_out, s, bpf);
     switch (ga.xform) {
